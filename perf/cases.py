@@ -78,8 +78,13 @@ def draw(rng):
         return {"kind": kind, "n": _log_int(rng, 10000, 1 << 26), "alpha": rng.choice([0.25, 0.5, 1.0]),
                 "staleness": rng.randint(0, 8)}
     cid = rng.choice(sorted(STEP))
-    lo, hi = STEP[cid][4], STEP[cid][3]
-    return {"kind": kind, "config": cid, "batch": _log_int(rng, lo, hi)}
+    _, shape, _, full, least, _, _, lo, _ = STEP[cid]
+    case = {"kind": kind, "config": cid, "batch": _log_int(rng, least, full if lo else 2 * full)}
+    if case["batch"] == full:  # listed
+        case["batch"] -= 1
+    if lo:  # a batch whose longest sequence is shorter than the network's
+        case["longest"] = rng.randint(2 * lo, shape[0])
+    return case
 
 
 # ------------------------------------------------------------------ the networks in plain torch
@@ -226,14 +231,20 @@ def forward(cid, net, x, lengths=None):
 _SHAPES = {}
 
 
-def shapes(cid):
+def _fill(cid, longest=None):
+    """The mean share of a sequence's tokens that are valid."""
+    _, shape, _, _, _, _, _, lo, _ = STEP[cid]
+    return (lo + (longest or shape[0])) / 2.0 / shape[0] if lo else 1.0
+
+
+def shapes(cid, fill=1.0):
     """(layout [(size, kind)], forward FLOPs of one sample, of them the first layer's)."""
-    if cid not in _SHAPES:
-        _, shape, _, _, _, _, _, lo, _ = STEP[cid]
-        net = Net(fill=(lo + shape[0]) / 2.0 / shape[0] if lo else 1.0)
+    if (cid, fill) not in _SHAPES:
+        shape = STEP[cid][1]
+        net = Net(fill=fill)
         forward(cid, net, torch.empty((1,) + shape, device="meta"))
-        _SHAPES[cid] = (net.layout, net.flops, net.first)
-    return _SHAPES[cid]
+        _SHAPES[cid, fill] = (net.layout, net.flops, net.first)
+    return _SHAPES[cid, fill]
 
 
 # ------------------------------------------------------------------ inputs
@@ -256,13 +267,15 @@ def _params(cid, gen):
     return flat
 
 
-def _acts(cid, batch, gen):
+def _acts(cid, batch, gen, longest=None):
     _, shape, classes, _, _, bf16, relu, lo, _ = STEP[cid]
     x = torch.randn((batch,) + shape, generator=gen, device="cuda")
     x = torch.relu(x) if relu else x
     x = x.bfloat16() if bf16 else x
     labels = torch.randint(0, classes, (batch,), generator=gen, device="cuda", dtype=torch.int32)
-    lengths = torch.randint(lo, shape[0] + 1, (batch,), generator=gen, device="cuda", dtype=torch.int32) if lo else None
+    if not lo:
+        return x, labels, None
+    lengths = torch.randint(lo, (longest or shape[0]) + 1, (batch,), generator=gen, device="cuda", dtype=torch.int32)
     return x, labels, lengths
 
 
@@ -288,9 +301,9 @@ class Buffers(dict):
 class Model:
     """A model handle (created for the workload's batch, as a server does) and its outputs."""
 
-    def __init__(self, cid, params):
+    def __init__(self, cid, params, batch):
         self.cid, self.more = cid, {}
-        self.model = A.fo_model_create(cid, STEP[cid][3], params.cpu().numpy(), torch.cuda.current_stream())
+        self.model = A.fo_model_create(cid, max(STEP[cid][3], batch), params.cpu().numpy(), torch.cuda.current_stream())
 
     def outputs(self):
         names = ["loss", "logits", "grads", "params"] + (["momentum"] if STEP[self.cid][8] else []) + list(self.more)
@@ -304,9 +317,9 @@ class Model:
 class Step(Model):
     def __init__(self, case, seed):
         gen = _generator(seed)
-        super().__init__(case["config"], _params(case["config"], gen))
+        super().__init__(case["config"], _params(case["config"], gen), case["batch"])
         self.batch = case["batch"]
-        self.x, self.labels, self.lengths = _acts(self.cid, self.batch, gen)
+        self.x, self.labels, self.lengths = _acts(self.cid, self.batch, gen, case.get("longest"))
         if self.cid == 6:
             self.more["sent"] = torch.empty((self.batch, 64, 16, 16), dtype=torch.bfloat16, device="cuda")
 
@@ -341,7 +354,7 @@ class Serve(Model):
 
     def __init__(self, case, seed):
         params, self.xs, self.labels, self.local, self.glob, self.turns = _serve_inputs(case, seed)
-        super().__init__(2, params)
+        super().__init__(2, params, case["batch"])
         K, B = case["devices"], case["batch"]
         self.xbytes = self.xs[0].numel() * 2
         self.queues = A.fo_queues_create(K, self.xbytes, B, False, 3 * K, torch.cuda.current_stream())
@@ -408,11 +421,11 @@ def run(state):
 
 
 # ------------------------------------------------------------------ what a pass cannot do without
-def _step_work(cid, batch):
-    layout, flops, first = shapes(cid)
-    _, shape, classes, _, _, bf16, _, lo, momentum = STEP[cid]
+def _step_work(cid, batch, longest=None):
+    fill = _fill(cid, longest)
+    layout, flops, first = shapes(cid, fill)
+    _, shape, classes, _, _, bf16, _, _, momentum = STEP[cid]
     n = sum(k for k, _ in layout)
-    fill = (lo + shape[0]) / 2.0 / shape[0] if lo else 1.0
     # parameters read and written, gradients written, momentum read and written, the batch read
     moved = 4.0 * n * (5 if momentum else 3) + batch * (math.prod(shape) * fill * (2 if bf16 else 4) + 4 + 4 * classes)
     if cid == 6:
@@ -424,7 +437,7 @@ def work(case):
     if case["kind"] == "aggregate":
         return {"bytes": 12.0 * case["n"], "flops": 2.0 * case["n"]}
     if case["kind"] == "step":
-        moved, flops = _step_work(case["config"], case["batch"])
+        moved, flops = _step_work(case["config"], case["batch"], case.get("longest"))
         return {"bytes": moved, "flops": flops}
     moved, flops = _step_work(2, case["batch"])
     K, n = case["devices"], case["agg_n"]
@@ -473,7 +486,7 @@ def exact(case, seed):
     if case["kind"] == "step":
         gen = _generator(seed)
         flat = _params(case["config"], gen)
-        return _exact_step(case["config"], flat, *_acts(case["config"], case["batch"], gen))
+        return _exact_step(case["config"], flat, *_acts(case["config"], case["batch"], gen, case.get("longest")))
     params, xs, labels, local, glob, turns = _serve_inputs(case, seed)
     # K + 1 batches were served while the pool was filled, device 0's second among them: device 1 has
     # the smallest count of those that wait, and its second batch is its oldest
