@@ -8,14 +8,27 @@
 // Transformer-6 has 5 heads of width 20 on 64-token batches, Transformer-12
 // 50 heads of width 2 on 256-token batches.
 //
-// The model is small (d = 100): the products run as LDS-tiled fp32 FMA
-// (64 x 64 output tiles, a deterministic split over K for the long weight-
-// gradient reductions), attention as one thread per query (forward, and the
-// dQ phase of the backward) or per key (the dK, dV phase) over K, V or Q, dO
-// staged in LDS, LayerNorm as one wave per row.  Batches stay padded
-// [B][L][d]; queries past a sequence's length are computed like the others
-// (nothing reads them, so their gradients are zero) and keys past it are masked.
-#include "gemm.h"
+// The model is small (d = 100: a layer is 60,000 weights), so a kernel per
+// product spends most of its time on the launch itself (about 4.5 us for each
+// dependent launch, whatever it does) and on a few workgroups walking a short
+// K.  Everything but the attention is local to a token's row, so a workgroup
+// takes 16 rows (one MFMA tile) of one sequence and carries them through a
+// whole layer in LDS:
+//   forward   [attention] -> output projection -> LN1 -> FFN -> LN2 -> the next layer's QKV
+//   backward  [attention of the layer above -> its QKV input gradient] -> LN2 -> FFN -> LN1 -> dO
+// on v_mfma_f32_16x16x4_f32 (fp32 operands and accumulation).  Attention needs
+// the whole sequence: with heads of width 20 it runs on the matrix cores at the
+// start of the same kernels (one launch per layer and direction), with heads of
+// width 2 (no contraction to speak of) in kernels of its own on the vector
+// units.  Weight gradients of every layer run as one launch at the end, bias
+// gradients with them (a column of ones), and one launch adds their slices,
+// the norms' column sums and updates the parameters.  Per step: 19 launches
+// (Transformer-6), 54 (Transformer-12), against 129 and 249 with one launch per
+// product; at batch 16, 282 us and 810-960 us against 1,042 and 3,046.
+// Rows past a sequence's length reach neither the loss nor a gradient, so only
+// the blocks of 16 rows that hold a valid token are computed; in the last layer
+// only the first token's block is (all that the classifier reads).
+#include "kernels.h"
 #include "model.h"
 
 namespace fo {
@@ -24,555 +37,1301 @@ namespace {
 
 constexpr int D = 100, FF = 100, NCLS = 2;
 constexpr float LN_EPS = 1e-5f;
+constexpr int BR = 16;          // rows of a block
+constexpr int ROW_T = 512;      // threads of a row kernel: 8 waves, 7 of them hold a 16-column block of d = 100
+constexpr float LOG2E = 1.4426950408889634f;
 
 struct Arch {
     int layers, heads, L;
 };
 Arch arch_of(int cid) { return cid == 7 ? Arch{6, 5, 64} : Arch{12, 50, 256}; }
 
-inline int nblk(int64_t n) { return (int)cdiv(n, 256); }
+// A block of rows: the first row's index in the [B][L] batch, the sequence, the
+// row's position in it and the sequence's (clamped) length.
+struct Blk {
+    int row0, b, r0, len;
+};
 
-using Gf = GemmF32;
-
-// ------------------------------------------------------------------ attention
-// Lengths as the kernels use them: clamped to [1, L]; the number of lengths
-// outside that range goes to *bad (the model's error flag).
-__global__ void lengths_check(const StepIn* __restrict__ in, int B, int L, float* __restrict__ bad) {
-    int n = 0;
-    for (int b = threadIdx.x; b < B; b += blockDim.x) n += in->lengths[b] < 1 || in->lengths[b] > L;
-    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
-    if (threadIdx.x == 0) *bad = (float)n;
-}
-__device__ __forceinline__ int seq_len(const StepIn* in, int b, int L) { return min(max(in->lengths[b], 1), L); }
-
-// One workgroup per (sequence, head); thread i is query i.  Keys and values of
-// the head in LDS; an online softmax over the valid keys (running maximum,
-// rescaled sum and output), then O and lse = max + log(sum).
-template <int DH>
-__global__ void __launch_bounds__(256) attn_small_fwd(const float* __restrict__ qkv, const StepIn* __restrict__ in,
-                                                      float* __restrict__ O, float* __restrict__ lse, int H, int L,
-                                                      float scale) {
-    extern __shared__ float sm[];
-    float* Ks = sm;
-    float* Vs = sm + L * DH;
-    const int b = blockIdx.x / H, h = blockIdx.x % H;
-    const int len = seq_len(in, b, L);
-    const int64_t row0 = (int64_t)b * L, ld = 3 * D;
-    for (int e = threadIdx.x; e < len * DH; e += blockDim.x) {
-        const int j = e / DH, c = e % DH;
-        Ks[e] = qkv[(row0 + j) * ld + D + h * DH + c];
-        Vs[e] = qkv[(row0 + j) * ld + 2 * D + h * DH + c];
+// ------------------------------------------------------------------ setup
+// The valid 16-row blocks, longest sequences first (ties by index) so that the
+// short ones fill in behind; their number goes to *nblk, the number of lengths
+// outside [1, L] (clamped) to *bad.  One workgroup, lengths in LDS.
+__global__ void __launch_bounds__(1024) tf_setup(const StepIn* __restrict__ in, int B, int L, Blk* __restrict__ blk,
+                                                 int* __restrict__ nblk, float* __restrict__ bad_out) {
+    extern __shared__ int lens[];
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    for (int b = threadIdx.x; b < B; b += blockDim.x) {
+        const int len = in->lengths[b];
+        if (len < 1 || len > L) atomicAdd(&bad, 1);
+        lens[b] = min(max(len, 1), L);
     }
     __syncthreads();
-    const int i = threadIdx.x;
-    if (i >= L) return;
-    float q[DH], acc[DH];
-#pragma unroll
-    for (int c = 0; c < DH; ++c) {
-        q[c] = qkv[(row0 + i) * ld + h * DH + c] * scale;
-        acc[c] = 0.f;
+    if (threadIdx.x == 0) *bad_out = (float)bad;
+    for (int b = threadIdx.x; b < B; b += blockDim.x) {
+        const int lb = lens[b], n = (lb + BR - 1) / BR;
+        int before = 0, off = 0;
+        for (int c = 0; c < B; ++c) {
+            const int lc = lens[c];
+            if (lc > lb || (lc == lb && c < b)) {
+                ++before;
+                off += (lc + BR - 1) / BR;
+            }
+        }
+        for (int i = 0; i < n; ++i) blk[off + i] = Blk{b * L + i * BR, b, i * BR, lb};
+        if (before == B - 1) *nblk = off + n;
     }
-    float mx = -INFINITY, sum = 0.f;
-    for (int j = 0; j < len; ++j) {
-        float s = 0.f;
-#pragma unroll
-        for (int c = 0; c < DH; ++c) s = fmaf(q[c], Ks[j * DH + c], s);
-        const float mn = fmaxf(mx, s);
-        // the hardware exponential (v_exp_f32 on x log2 e): its error on these
-        // arguments (<= 0 after the running-max shift) is far below the fp32 path's
-        const float f = __expf(mx - mn), p = __expf(s - mn);  // exp(-inf) = 0 on the first key
-        sum = sum * f + p;
-#pragma unroll
-        for (int c = 0; c < DH; ++c) acc[c] = fmaf(acc[c], f, p * Vs[j * DH + c]);
-        mx = mn;
-    }
-    const float inv = 1.f / sum;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) O[(row0 + i) * D + h * DH + c] = acc[c] * inv;
-    lse[(int64_t)blockIdx.x * L + i] = mx + logf(sum);
 }
 
-// Backward, with P = softmax(S), D_i = dO_i . O_i, dS_ij = P_ij (dO_i . V_j - D_i):
-// phase 1, thread = query i: dQ_i = scale sum_j dS_ij K_j (K, V in LDS);
-// phase 2, thread = key j: dK_j = scale sum_i dS_ij Q_i, dV_j = sum_i P_ij dO_i
-// over every query (Q, dO, lse, D in LDS).  Keys past the length get zero.
-template <int DH>
-__global__ void __launch_bounds__(256) attn_small_bwd(const float* __restrict__ qkv, const StepIn* __restrict__ in,
-                                                      const float* __restrict__ O, const float* __restrict__ dO,
-                                                      const float* __restrict__ lse, float* __restrict__ dqkv, int H,
-                                                      int L, float scale) {
-    extern __shared__ float sm[];
-    float* T0 = sm;                // K, then Q
-    float* T1 = sm + L * DH;       // V, then dO
-    float* Ls = sm + 2 * L * DH;   // lse
-    float* Ds = Ls + L;            // D
-    const int b = blockIdx.x / H, h = blockIdx.x % H;
-    const int len = seq_len(in, b, L);
-    const int64_t row0 = (int64_t)b * L, ld = 3 * D;
+// ------------------------------------------------------------------ 16 x 16 tiles on fp32 MFMA
+// v_mfma_f32_16x16x4_f32: lane l holds A(row l % 16, k = l / 16), B(k = l / 16,
+// column l % 16) and, of the result, rows 4 (l / 16) .. + 3 of column l % 16.
+// The order of k is free as long as both operands share it: lane group g takes
+// k = 16 s + 4 g + j in instruction j of step s, so an operand whose k is
+// contiguous is one 16-byte load per step, and the last K % 16 (a multiple of
+// 4) go four at a time.
+template <int K>
+struct Frag {
+    static constexpr int S = K / 16, T = K % 16 / 4;
+    f32x4 v[S];
+    float t[T ? T : 1];
+};
+// The lane's row of an operand with k contiguous (16-byte aligned).
+template <int K>
+__device__ __forceinline__ void frag_row(Frag<K>& f, const float* row, int g) {
+#pragma unroll
+    for (int s = 0; s < Frag<K>::S; ++s) f.v[s] = *reinterpret_cast<const f32x4*>(row + 16 * s + 4 * g);
+#pragma unroll
+    for (int j = 0; j < Frag<K>::T; ++j) f.t[j] = row[16 * Frag<K>::S + 4 * j + g];
+}
+// The lane's column of an operand whose k is strided by ld (p: element k = 0).
+template <int K>
+__device__ __forceinline__ void frag_col(Frag<K>& f, const float* p, int ld, int g) {
+#pragma unroll
+    for (int s = 0; s < Frag<K>::S; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f.v[s][j] = p[(16 * s + 4 * g + j) * ld];
+#pragma unroll
+    for (int j = 0; j < Frag<K>::T; ++j) f.t[j] = p[(16 * Frag<K>::S + 4 * j + g) * ld];
+}
+__device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// Four partial sums (one per j), added pairwise at the end: shorter chains of
+// dependent MFMAs and a smaller rounding error than one running sum.
+template <int K>
+__device__ __forceinline__ f32x4 mma(const Frag<K>& a, const Frag<K>& b) {
+    f32x4 c[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < Frag<K>::S; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = mfma(a.v[s][j], b.v[s][j], c[j]);
+#pragma unroll
+    for (int j = 0; j < Frag<K>::T; ++j) c[j] = mfma(a.t[j], b.t[j], c[j]);
+    return (c[0] + c[1]) + (c[2] + c[3]);
+}
+
+// Barrier for data exchanged through LDS only: the waits for global loads and
+// stores that __syncthreads() implies would end the weight prefetch here.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ void st4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
+__device__ __forceinline__ float sum32(float v) {
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+// A 16-row block of a [rows][100] matrix, contiguous, into LDS.
+__device__ __forceinline__ void load_block(float* s, const float* g) {
+    if (threadIdx.x < BR * D / 4) st4(s + 4 * threadIdx.x, ld4(g + 4 * threadIdx.x));
+}
+// The same from the batch as sent: rows past the length are taken as zero.
+__device__ __forceinline__ f32x4 batch4(const StepIn* in, const Blk& q, int e) {
+    const int row = 4 * e / D;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    return q.r0 + row < q.len ? ld4(static_cast<const float*>(in->x) + (int64_t)q.row0 * D + 4 * e) : zero;
+}
+
+// ------------------------------------------------------------------ LayerNorm of a block: half a wave per row
+struct LnParam {
+    float g[4], b[4];
+};
+__device__ __forceinline__ LnParam ln_param(const float* g, const float* b) {
+    LnParam p;
+    const int q = threadIdx.x & 31;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = min(q + 32 * j, D - 1);
+        p.g[j] = g[c];
+        p.b[j] = b ? b[c] : 0.f;
+    }
+    return p;
+}
+// u (LDS) -> y (LDS and global), xhat and 1 / sigma (global); row0: the block's first row.
+__device__ __forceinline__ void ln_fwd(const float* u, const LnParam& p, float* ys, float* y, float* xhat, float* rstd,
+                                       int row0) {
+    const int r = threadIdx.x >> 5, q = threadIdx.x & 31;
+    float x[4], s = 0.f, v = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = q + 32 * j;
+        x[j] = c < D ? u[r * D + c] : 0.f;
+        s += x[j];
+    }
+    const float mu = sum32(s) / D;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        x[j] = q + 32 * j < D ? x[j] - mu : 0.f;
+        v = fmaf(x[j], x[j], v);
+    }
+    const float rs = 1.f / sqrtf(sum32(v) / D + LN_EPS);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = q + 32 * j;
+        if (c < D) {
+            const float xh = x[j] * rs, o = xh * p.g[j] + p.b[j];
+            ys[r * D + c] = o;
+            y[(int64_t)row0 * D + r * D + c] = o;
+            xhat[(int64_t)row0 * D + r * D + c] = xh;
+        }
+    }
+    if (q == 0) rstd[row0 + r] = rs;
+}
+// The row's xhat and 1 / sigma for the backward (loaded ahead of their use).
+struct LnSaved {
+    float xh[4], rs;
+};
+__device__ __forceinline__ LnSaved ln_saved(const float* xhat, const float* rstd, int row0) {
+    LnSaved s;
+    const int r = threadIdx.x >> 5, q = threadIdx.x & 31;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s.xh[j] = xhat[(int64_t)(row0 + r) * D + min(q + 32 * j, D - 1)];
+    s.rs = rstd[row0 + r];
+    return s;
+}
+// dx = rstd (dy g - mean(dy g) - xhat mean(dy g xhat)) into LDS and global; xhat also into LDS.
+__device__ __forceinline__ void ln_bwd(const float* dy, const LnSaved& sv, const LnParam& p, float* xs, float* dxs,
+                                       float* dx, int row0) {
+    const int r = threadIdx.x >> 5, q = threadIdx.x & 31;
+    float ga[4], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = q + 32 * j;
+        ga[j] = c < D ? dy[r * D + c] * p.g[j] : 0.f;
+        s1 += ga[j];
+        s2 = fmaf(ga[j], sv.xh[j], s2);
+    }
+    s1 = sum32(s1) / D;
+    s2 = sum32(s2) / D;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int c = q + 32 * j;
+        if (c < D) {
+            const float o = sv.rs * (ga[j] - s1 - sv.xh[j] * s2);
+            xs[r * D + c] = sv.xh[j];
+            dxs[r * D + c] = o;
+            dx[(int64_t)row0 * D + r * D + c] = o;
+        }
+    }
+}
+// The block's share of the norm's parameter gradients: part[0][c] = sum dy xhat, part[1][c] = sum dy.
+__device__ __forceinline__ void ln_cols(const float* dy, const float* xs, float* part) {
     const int t = threadIdx.x;
-    for (int e = t; e < len * DH; e += blockDim.x) {
-        const int j = e / DH, c = e % DH;
-        T0[e] = qkv[(row0 + j) * ld + D + h * DH + c];
-        T1[e] = qkv[(row0 + j) * ld + 2 * D + h * DH + c];
-    }
-    float dsum = 0.f, li = 0.f;
-    float q[DH], g[DH];
-    if (t < L) {
+    if (t >= 2 * D) return;
+    const int c = t % D;
+    float s = 0.f;
 #pragma unroll
-        for (int c = 0; c < DH; ++c) {
-            q[c] = qkv[(row0 + t) * ld + h * DH + c];
-            g[c] = dO[(row0 + t) * D + h * DH + c];
-            dsum = fmaf(g[c], O[(row0 + t) * D + h * DH + c], dsum);
+    for (int r = 0; r < BR; ++r) s = t < D ? fmaf(dy[r * D + c], xs[r * D + c], s) : s + dy[r * D + c];
+    part[t] = s;
+}
+
+// ------------------------------------------------------------------ attention, heads of width 20 (L = 64): MFMA
+// Scores are kept transposed (a lane owns a query column, its group g the keys
+// 16 kb + 4 g + i), so the softmax reduces within the lane and over the four
+// groups, and P^T is already the B operand of O^T = V^T P^T.  Base-2
+// exponentials, lse in base 2.  Every load of a head is issued at once, at rows
+// clamped into the valid blocks; masked keys get weight zero.
+constexpr int H20 = 5, W20 = 20, KB20 = 4;
+
+__device__ __forceinline__ void att20_fwd(const float* __restrict__ qkv, const Blk& q, int h, float sc2, float* so,
+                                          float* __restrict__ O, float* __restrict__ lse) {
+    const int tok = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    const int top = (q.len + BR - 1) / BR * BR - 1;  // last computed row of the sequence
+    const float* seq = qkv + (int64_t)(q.row0 - q.r0) * 3 * D + h * W20;
+    Frag<W20> qf, kf[KB20];
+    frag_row(qf, seq + (q.r0 + tok) * 3 * D, g);
+#pragma unroll
+    for (int kb = 0; kb < KB20; ++kb) frag_row(kf[kb], seq + min(16 * kb + tok, top) * 3 * D + D, g);
+    float v0[KB20][4], v1[KB20][4];
+#pragma unroll
+    for (int kb = 0; kb < KB20; ++kb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float* v = seq + min(16 * kb + 4 * g + j, top) * 3 * D + 2 * D;
+            v0[kb][j] = v[tok];
+            v1[kb][j] = v[16 + (tok & 3)];
         }
-        li = lse[(int64_t)blockIdx.x * L + t];
+    f32x4 s[KB20];
+    float m = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < KB20; ++kb) {
+        s[kb] = mma(kf[kb], qf);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (16 * kb + 4 * g + i >= q.len) s[kb][i] = -INFINITY;
+            m = fmaxf(m, s[kb][i]);
+        }
+    }
+    m = fmaxf(m, __shfl_xor(m, 16));
+    m = fmaxf(m, __shfl_xor(m, 32)) * sc2;
+    float l = 0.f;
+    f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0;
+#pragma unroll
+    for (int kb = 0; kb < KB20; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(s[kb][i], sc2, -m));
+            l += p;
+            o0 = mfma(v0[kb][i], p, o0);
+            o1 = mfma(v1[kb][i], p, o1);
+        }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    const float inv = 1.f / l;
+    const int c = h * W20 + 4 * g;
+    o0 *= inv;
+    o1 *= inv;
+    st4(so + tok * D + c, o0);
+    st4(O + (int64_t)(q.row0 + tok) * D + c, o0);
+    if (g == 0) {
+        st4(so + tok * D + c + 16, o1);
+        st4(O + (int64_t)(q.row0 + tok) * D + c + 16, o1);
+        lse[(int64_t)(q.row0 + tok) * H20 + h] = m + __builtin_amdgcn_logf(l);
+    }
+}
+
+// dQ of the block's rows (head h) into sq (LDS, [16][300], columns 20 h ..):
+// dS^T = P^T (V dO^T - D), dQ^T = K^T dS^T.  qlimit: queries from there on have no gradient.
+__device__ __forceinline__ void att20_dq(const float* __restrict__ qkv, const float* __restrict__ dO,
+                                         const float* __restrict__ lse, const float* __restrict__ Dv, const Blk& q,
+                                         int qlimit, int h, float scale, float* sq) {
+    const int tok = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    const int top = (q.len + BR - 1) / BR * BR - 1;
+    const float* seq = qkv + (int64_t)(q.row0 - q.r0) * 3 * D + h * W20;
+    Frag<W20> qf, gf, kf[KB20], vf[KB20];
+    frag_row(qf, seq + (q.r0 + tok) * 3 * D, g);
+    frag_row(gf, dO + (int64_t)(q.row0 + tok) * D + h * W20, g);
+    const float ls = lse[(int64_t)(q.row0 + tok) * H20 + h], dv = Dv[(int64_t)(q.row0 + tok) * H20 + h];
+    float k0[KB20][4], k1[KB20][4];
+#pragma unroll
+    for (int kb = 0; kb < KB20; ++kb) {
+        const float* kr = seq + min(16 * kb + tok, top) * 3 * D + D;
+        frag_row(kf[kb], kr, g);
+        frag_row(vf[kb], kr + D, g);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float* k = seq + min(16 * kb + 4 * g + j, top) * 3 * D + D;
+            k0[kb][j] = k[tok];
+            k1[kb][j] = k[16 + (tok & 3)];
+        }
+    }
+    const bool row = q.r0 + tok < qlimit;
+    f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+#pragma unroll
+    for (int kb = 0; kb < KB20; ++kb) {
+        const f32x4 s = mma(kf[kb], qf), dp = mma(vf[kb], gf);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float p = __builtin_amdgcn_exp2f(fmaf(s[i], scale * LOG2E, -ls));
+            const float ds = row && 16 * kb + 4 * g + i < q.len ? p * (dp[i] - dv) : 0.f;
+            a0 = mfma(k0[kb][i], ds, a0);
+            a1 = mfma(k1[kb][i], ds, a1);
+        }
+    }
+    a0 *= scale;
+    a1 *= scale;
+    st4(sq + tok * 3 * D + h * W20 + 4 * g, a0);
+    if (g == 0) st4(sq + tok * 3 * D + h * W20 + 16, a1);
+}
+
+// dK and dV of the block's rows (head h) into sq: over the queries below qlimit,
+// dV^T = dO^T P, dK^T = Q^T dS (a lane owns a key column, its group the queries).
+__device__ __forceinline__ void att20_dkv(const float* __restrict__ qkv, const float* __restrict__ dO,
+                                          const float* __restrict__ lse, const float* __restrict__ Dv, const Blk& q,
+                                          int qlimit, int h, float scale, float* sq) {
+    const int tok = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    const int last = (qlimit + BR - 1) / BR * BR - 1;  // last row with a stored gradient
+    const int64_t s0 = q.row0 - q.r0;
+    const float* seq = qkv + s0 * 3 * D + h * W20;
+    Frag<W20> kf, vf;
+    frag_row(kf, seq + (q.r0 + tok) * 3 * D + D, g);
+    frag_row(vf, seq + (q.r0 + tok) * 3 * D + 2 * D, g);
+    const bool key = q.r0 + tok < q.len;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 dk0 = zero, dk1 = zero, dv0 = zero, dv1 = zero;
+#pragma unroll 2
+    for (int qb = 0; qb < KB20; ++qb) {
+        Frag<W20> qf, gf;
+        const int r = min(16 * qb + tok, last);
+        frag_row(qf, seq + r * 3 * D, g);
+        frag_row(gf, dO + (s0 + r) * D + h * W20, g);
+        float ls[4], dd[4], q0[4], q1[4], g0[4], g1[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int rj = min(16 * qb + 4 * g + j, last);
+            ls[j] = lse[(s0 + rj) * H20 + h];
+            dd[j] = Dv[(s0 + rj) * H20 + h];
+            q0[j] = seq[rj * 3 * D + tok];
+            q1[j] = seq[rj * 3 * D + 16 + (tok & 3)];
+            g0[j] = dO[(s0 + rj) * D + h * W20 + tok];
+            g1[j] = dO[(s0 + rj) * D + h * W20 + 16 + (tok & 3)];
+        }
+        const f32x4 s = mma(qf, kf), dp = mma(gf, vf);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool on = key && 16 * qb + 4 * g + i < qlimit;
+            const float p = on ? __builtin_amdgcn_exp2f(fmaf(s[i], scale * LOG2E, -ls[i])) : 0.f;
+            const float ds = on ? p * (dp[i] - dd[i]) : 0.f;
+            dv0 = mfma(g0[i], p, dv0);
+            dv1 = mfma(g1[i], p, dv1);
+            dk0 = mfma(q0[i], ds, dk0);
+            dk1 = mfma(q1[i], ds, dk1);
+        }
+    }
+    dk0 *= scale;
+    dk1 *= scale;
+    float* o = sq + tok * 3 * D + D + h * W20;
+    st4(o + 4 * g, dk0);
+    st4(o + D + 4 * g, dv0);
+    if (g == 0) {
+        st4(o + 16, dk1);
+        st4(o + D + 16, dv1);
+    }
+}
+
+// The attention backward of a block with heads of width 20: ten tasks (dK / dV
+// of five heads, then dQ) over the eight waves, the block's dqkv rows in LDS
+// and then to memory (the QKV weight gradient reads them).
+__device__ __forceinline__ void att20_bwd(const float* qkv, const float* dO, const float* lse, const float* Dv,
+                                          const Blk& q, int qlimit, float scale, float* sq, float* dqkv) {
+    for (int t = threadIdx.x >> 6; t < 2 * H20; t += ROW_T / 64) {
+        if (t < H20)
+            att20_dkv(qkv, dO, lse, Dv, q, qlimit, t, scale, sq);
+        else
+            att20_dq(qkv, dO, lse, Dv, q, qlimit, t - H20, scale, sq);
+    }
+    lds_barrier();
+    for (int e = threadIdx.x; e < BR * 3 * D / 4; e += ROW_T) st4(dqkv + (int64_t)q.row0 * 3 * D + 4 * e, ld4(sq + 4 * e));
+}
+
+// ------------------------------------------------------------------ attention, heads of width 2 (L = 256): vector units
+// A score is two multiply-adds, so the exponential and its neighbours bound
+// these kernels (about 11 cycles of a SIMD per 64 scores in the forward), not a
+// contraction.  A workgroup takes 8 rows of a sequence; thread = (one eighth of
+// the other side, 4 of the 8 rows, head): each loaded key (query) serves four
+// rows, the 50 heads of a row are consecutive lanes, and the eighths are merged
+// in order through LDS.
+constexpr int H2 = 50, AR = 8, AQ = 4, AS = 8;
+constexpr int ATT_T = 832;  // 800 threads of work: 8 x 2 x 50
+
+struct Part2 {
+    int s, row, h, lo, hi;  // eighth, first of the thread's rows (0 or 4), head, its share [lo, hi) of n
+};
+__device__ __forceinline__ Part2 part2(int n) {
+    Part2 p;
+    p.s = threadIdx.x / (2 * H2);
+    p.row = threadIdx.x % (2 * H2) / H2 * AQ;
+    p.h = threadIdx.x % H2;
+    const int per = (n + 4 * AS - 1) / (4 * AS) * 4;
+    p.lo = min(p.s * per, n);
+    p.hi = min(p.lo + per, n);
+    return p;
+}
+
+// O and lse (base 2) of 8 rows.  top: only the first token's rows are wanted.
+__global__ void __launch_bounds__(ATT_T) att2_fwd(const float* __restrict__ qkv, const Blk* __restrict__ blk,
+                                                  const int* __restrict__ nblk, int top, float* __restrict__ O,
+                                                  float* __restrict__ lse, float scale) {
+    __shared__ f32x4 red[AS][AR * H2];
+    if ((int)blockIdx.x / 2 >= *nblk) return;
+    const Blk q = blk[blockIdx.x / 2];
+    const int r0 = q.r0 + (blockIdx.x & 1) * AR;  // position of the first of the 8 rows
+    if (top && q.r0 > 0) return;
+    const int64_t s0 = q.row0 - q.r0;
+    const Part2 t = part2(q.len);
+    if (threadIdx.x < 2 * H2 * AS) {
+        const float* seq = qkv + s0 * 3 * D + 2 * t.h;
+        float q0[AQ], q1[AQ], m[AQ], l[AQ], a0[AQ], a1[AQ];
+#pragma unroll
+        for (int u = 0; u < AQ; ++u) {
+            const float2 v = *reinterpret_cast<const float2*>(seq + (r0 + t.row + u) * 3 * D);
+            q0[u] = v.x * (scale * LOG2E);
+            q1[u] = v.y * (scale * LOG2E);
+            m[u] = -INFINITY;
+            l[u] = a0[u] = a1[u] = 0.f;
+        }
+        for (int j = t.lo; j < t.hi; j += 4) {
+            float2 k[4], v[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float* r = seq + min(j + c, t.hi - 1) * 3 * D;
+                k[c] = *reinterpret_cast<const float2*>(r + D);
+                v[c] = *reinterpret_cast<const float2*>(r + 2 * D);
+            }
+#pragma unroll
+            for (int u = 0; u < AQ; ++u) {
+                float s[4], mn = m[u];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    s[c] = j + c < t.hi ? fmaf(q0[u], k[c].x, q1[u] * k[c].y) : -INFINITY;
+                    mn = fmaxf(mn, s[c]);
+                }
+                const float f = __builtin_amdgcn_exp2f(m[u] - mn);  // exp2(-inf) = 0 at the first keys
+                l[u] *= f;
+                a0[u] *= f;
+                a1[u] *= f;
+                m[u] = mn;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float p = __builtin_amdgcn_exp2f(s[c] - mn);
+                    l[u] += p;
+                    a0[u] = fmaf(p, v[c].x, a0[u]);
+                    a1[u] = fmaf(p, v[c].y, a1[u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < AQ; ++u) red[t.s][(t.row + u) * H2 + t.h] = f32x4{m[u], l[u], a0[u], a1[u]};
     }
     __syncthreads();
-    if (t < L) {
-        float dq[DH];
+    if (threadIdx.x >= AR * H2) return;
+    f32x4 v[AS];
+    float m = -INFINITY, l = 0.f, a0 = 0.f, a1 = 0.f;
 #pragma unroll
-        for (int c = 0; c < DH; ++c) dq[c] = 0.f;
-        for (int j = 0; j < len; ++j) {
-            float s = 0.f, dp = 0.f;
-#pragma unroll
-            for (int c = 0; c < DH; ++c) {
-                s = fmaf(q[c], T0[j * DH + c], s);
-                dp = fmaf(g[c], T1[j * DH + c], dp);
-            }
-            const float p = __expf(s * scale - li), ds = p * (dp - dsum);
-#pragma unroll
-            for (int c = 0; c < DH; ++c) dq[c] = fmaf(ds, T0[j * DH + c], dq[c]);
-        }
-#pragma unroll
-        for (int c = 0; c < DH; ++c) dqkv[(row0 + t) * ld + h * DH + c] = dq[c] * scale;
+    for (int s = 0; s < AS; ++s) {
+        v[s] = red[s][threadIdx.x];
+        m = fmaxf(m, v[s][0]);
     }
-    __syncthreads();  // phase 2 overwrites K, V with Q, dO
-    if (t < L) {
 #pragma unroll
-        for (int c = 0; c < DH; ++c) {
-            T0[t * DH + c] = q[c];
-            T1[t * DH + c] = g[c];
+    for (int s = 0; s < AS; ++s) {
+        const float f = __builtin_amdgcn_exp2f(v[s][0] - m);  // a share without keys: exp2(-inf) = 0
+        l = fmaf(f, v[s][1], l);
+        a0 = fmaf(f, v[s][2], a0);
+        a1 = fmaf(f, v[s][3], a1);
+    }
+    const int row = threadIdx.x / H2, h = threadIdx.x % H2;
+    const float inv = 1.f / l;
+    *reinterpret_cast<float2*>(O + (s0 + r0 + row) * D + 2 * h) = make_float2(a0 * inv, a1 * inv);
+    lse[(s0 + r0 + row) * H2 + h] = m + __builtin_amdgcn_logf(l);
+}
+
+// dQ (blockIdx.y = 0: the rows as queries over the keys) or dK and dV
+// (blockIdx.y = 1: the rows as keys over the queries below the limit) of 8 rows.
+__global__ void __launch_bounds__(ATT_T) att2_bwd(const float* __restrict__ qkv, const float* __restrict__ dO,
+                                                  const float* __restrict__ lse, const float* __restrict__ Dv,
+                                                  const Blk* __restrict__ blk, const int* __restrict__ nblk, int top,
+                                                  float* __restrict__ dqkv, float scale) {
+    __shared__ f32x4 red[AS][AR * H2];
+    if ((int)blockIdx.x / 2 >= *nblk) return;
+    const Blk q = blk[blockIdx.x / 2];
+    const int r0 = q.r0 + (blockIdx.x & 1) * AR;
+    const int64_t s0 = q.row0 - q.r0;
+    const int qlimit = top ? 1 : q.len;  // queries from there on have no gradient
+    const bool work = threadIdx.x < 2 * H2 * AS;
+    const float sc2 = scale * LOG2E;
+    if (blockIdx.y == 0) {
+        const Part2 t = part2(r0 < qlimit ? q.len : 0);
+        if (work) {
+            const float* seq = qkv + s0 * 3 * D + 2 * t.h;
+            float q0[AQ], q1[AQ], g0[AQ], g1[AQ], ls[AQ], dd[AQ], a0[AQ], a1[AQ];
+#pragma unroll
+            for (int u = 0; u < AQ; ++u) {
+                const int64_t r = r0 + t.row + u;
+                const float2 v = *reinterpret_cast<const float2*>(seq + r * 3 * D);
+                const float2 w = *reinterpret_cast<const float2*>(dO + (s0 + r) * D + 2 * t.h);
+                q0[u] = v.x * sc2;
+                q1[u] = v.y * sc2;
+                g0[u] = w.x;
+                g1[u] = w.y;
+                ls[u] = lse[(s0 + r) * H2 + t.h];
+                dd[u] = Dv[(s0 + r) * H2 + t.h];
+                a0[u] = a1[u] = 0.f;
+            }
+            for (int j = t.lo; j < t.hi; j += 4) {
+                float2 k[4], v[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float* r = seq + min(j + c, t.hi - 1) * 3 * D;
+                    k[c] = *reinterpret_cast<const float2*>(r + D);
+                    v[c] = *reinterpret_cast<const float2*>(r + 2 * D);
+                }
+#pragma unroll
+                for (int u = 0; u < AQ; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float p = __builtin_amdgcn_exp2f(fmaf(q0[u], k[c].x, fmaf(q1[u], k[c].y, -ls[u])));
+                        const float dp = fmaf(g0[u], v[c].x, fmaf(g1[u], v[c].y, -dd[u]));
+                        const float ds = j + c < t.hi ? p * dp : 0.f;
+                        a0[u] = fmaf(ds, k[c].x, a0[u]);
+                        a1[u] = fmaf(ds, k[c].y, a1[u]);
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < AQ; ++u) red[t.s][(t.row + u) * H2 + t.h] = f32x4{a0[u], a1[u], 0.f, 0.f};
         }
-        Ls[t] = li;
-        Ds[t] = dsum;
+    } else {
+        const Part2 t = part2(r0 < q.len ? qlimit : 0);
+        if (work) {
+            const float* seq = qkv + s0 * 3 * D + 2 * t.h;
+            float k0[AQ], k1[AQ], v0[AQ], v1[AQ];
+            f32x4 a[AQ];
+#pragma unroll
+            for (int u = 0; u < AQ; ++u) {
+                const float* r = seq + (r0 + t.row + u) * 3 * D;
+                const float2 k = *reinterpret_cast<const float2*>(r + D);
+                const float2 v = *reinterpret_cast<const float2*>(r + 2 * D);
+                k0[u] = k.x * sc2;
+                k1[u] = k.y * sc2;
+                v0[u] = v.x;
+                v1[u] = v.y;
+                a[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            for (int j = t.lo; j < t.hi; j += 4) {
+                float2 x[4], w[4];
+                float ls[4], dd[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int64_t r = min(j + c, t.hi - 1);
+                    x[c] = *reinterpret_cast<const float2*>(seq + r * 3 * D);
+                    w[c] = *reinterpret_cast<const float2*>(dO + (s0 + r) * D + 2 * t.h);
+                    ls[c] = lse[(s0 + r) * H2 + t.h];
+                    dd[c] = Dv[(s0 + r) * H2 + t.h];
+                }
+#pragma unroll
+                for (int u = 0; u < AQ; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float e = __builtin_amdgcn_exp2f(fmaf(x[c].x, k0[u], fmaf(x[c].y, k1[u], -ls[c])));
+                        const float p = j + c < t.hi ? e : 0.f;
+                        const float ds = p * fmaf(w[c].x, v0[u], fmaf(w[c].y, v1[u], -dd[c]));
+                        a[u][0] = fmaf(ds, x[c].x, a[u][0]);
+                        a[u][1] = fmaf(ds, x[c].y, a[u][1]);
+                        a[u][2] = fmaf(p, w[c].x, a[u][2]);
+                        a[u][3] = fmaf(p, w[c].y, a[u][3]);
+                    }
+            }
+#pragma unroll
+            for (int u = 0; u < AQ; ++u) red[t.s][(t.row + u) * H2 + t.h] = a[u];
+        }
     }
     __syncthreads();
-    if (t >= L) return;
-    float kj[DH], vj[DH], dk[DH], dv[DH];
-    const bool valid = t < len;
+    if (threadIdx.x >= AR * H2) return;
+    f32x4 a = red[0][threadIdx.x];
 #pragma unroll
-    for (int c = 0; c < DH; ++c) {
-        kj[c] = valid ? qkv[(row0 + t) * ld + D + h * DH + c] : 0.f;
-        vj[c] = valid ? qkv[(row0 + t) * ld + 2 * D + h * DH + c] : 0.f;
-        dk[c] = dv[c] = 0.f;
-    }
-    if (valid)
-        for (int i = 0; i < L; ++i) {
-            float s = 0.f, dp = 0.f;
-#pragma unroll
-            for (int c = 0; c < DH; ++c) {
-                s = fmaf(T0[i * DH + c], kj[c], s);
-                dp = fmaf(T1[i * DH + c], vj[c], dp);
-            }
-            const float p = __expf(s * scale - Ls[i]), ds = p * (dp - Ds[i]);
-#pragma unroll
-            for (int c = 0; c < DH; ++c) {
-                dk[c] = fmaf(ds, T0[i * DH + c], dk[c]);
-                dv[c] = fmaf(p, T1[i * DH + c], dv[c]);
-            }
-        }
-#pragma unroll
-    for (int c = 0; c < DH; ++c) {
-        dqkv[(row0 + t) * ld + D + h * DH + c] = dk[c] * scale;
-        dqkv[(row0 + t) * ld + 2 * D + h * DH + c] = dv[c];
+    for (int s = 1; s < AS; ++s) a += red[s][threadIdx.x];
+    const int row = threadIdx.x / H2, h = threadIdx.x % H2;
+    float* o = dqkv + (s0 + r0 + row) * 3 * D + 2 * h;
+    if (blockIdx.y == 0) {
+        const float f = r0 + row < qlimit ? scale : 0.f;  // (rows without a gradient summed unread operands)
+        *reinterpret_cast<float2*>(o) = f != 0.f ? make_float2(a[0] * f, a[1] * f) : make_float2(0.f, 0.f);
+    } else {
+        const bool key = r0 + row < q.len;
+        *reinterpret_cast<float2*>(o + D) = key ? make_float2(a[0] * scale, a[1] * scale) : make_float2(0.f, 0.f);
+        *reinterpret_cast<float2*>(o + 2 * D) = key ? make_float2(a[2], a[3]) : make_float2(0.f, 0.f);
     }
 }
 
-// ------------------------------------------------------------------ LayerNorm (d = 100, one wave per row)
-__global__ void __launch_bounds__(256) ln_small_fwd(const float* __restrict__ u, const float* __restrict__ gam,
-                                                    const float* __restrict__ bet, float* __restrict__ y,
-                                                    float* __restrict__ xhat, float* __restrict__ rstd, int rows) {
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
-    if (r >= rows) return;
-    const float* x = u + (int64_t)r * D;
-    const float a = x[l], c = l + 64 < D ? x[l + 64] : 0.f;
-    float s = a + c;
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    const float mu = s / D, da = a - mu, dc = l + 64 < D ? c - mu : 0.f;
-    float v = da * da + dc * dc;
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    const float rs = 1.f / sqrtf(v / D + LN_EPS);
-    const int64_t o0 = (int64_t)r * D;
-    xhat[o0 + l] = da * rs;
-    y[o0 + l] = da * rs * gam[l] + bet[l];
-    if (l + 64 < D) {
-        xhat[o0 + l + 64] = dc * rs;
-        y[o0 + l + 64] = dc * rs * gam[l + 64] + bet[l + 64];
-    }
-    if (l == 0) rstd[r] = rs;
-}
-
-// dx = rstd (dy g - mean(dy g) - xhat mean(dy g xhat)) (+ add); also dy * xhat
-// into gx for the scale gradient's column sums.
-__global__ void __launch_bounds__(256) ln_small_bwd(const float* __restrict__ dy, const float* __restrict__ xhat,
-                                                    const float* __restrict__ rstd, const float* __restrict__ gam,
-                                                    float* __restrict__ dx, float* __restrict__ gx, int rows) {
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), l = threadIdx.x & 63;
-    if (r >= rows) return;
-    const int64_t o0 = (int64_t)r * D;
-    const bool two = l + 64 < D;
-    const float ya = dy[o0 + l], yc = two ? dy[o0 + l + 64] : 0.f;
-    const float xa = xhat[o0 + l], xc = two ? xhat[o0 + l + 64] : 0.f;
-    const float ga = ya * gam[l], gc = two ? yc * gam[l + 64] : 0.f;
-    float s1 = ga + gc, s2 = ga * xa + gc * xc;
-    for (int o = 32; o > 0; o >>= 1) {
-        s1 += __shfl_xor(s1, o);
-        s2 += __shfl_xor(s2, o);
-    }
-    s1 /= D;
-    s2 /= D;
-    const float rs = rstd[r];
-    dx[o0 + l] = rs * (ga - s1 - xa * s2);
-    gx[o0 + l] = ya * xa;
-    if (two) {
-        dx[o0 + l + 64] = rs * (gc - s1 - xc * s2);
-        gx[o0 + l + 64] = yc * xc;
-    }
-}
-
-// ------------------------------------------------------------------ plan
-struct LayerP {
+// ------------------------------------------------------------------ a layer's rows, forward
+struct LayerW {
     const float *wqkv, *bqkv, *wo, *bo, *g1, *b1n, *w1, *b1, *w2, *b2, *g2, *b2n;
-    float *gwqkv, *gbqkv, *gwo, *gbo, *gg1, *gb1n, *gw1, *gb1, *gw2, *gb2, *gg2, *gb2n;
-    // saved activations
+};
+// Saved activations of a layer.
+struct LayerA {
     float *qkv, *O, *lse, *xh1, *rs1, *h1, *f, *xh2, *rs2, *y;
 };
 
-struct Plan {
-    Arch a;
-    LayerP* ly;        // [layers] (host array)
-    const float *wc, *bc;
-    float *gwc, *gbc;
-    float *dz, *dy, *du2, *df, *dh1, *du1, *dO, *dqkv, *dx, *gx, *gx1;
-    float* part;       // split-K slices
-    float* colws;      // column-sum workspace
-    float* sumws;      // partial rows of a layer's kLayerSums column sums
-    float* wgpart;     // the weight gradients' K slices of every layer (layer_wgrad_part each)
-    size_t part_floats;
+// A 16 x 300 block of the QKV projection of the rows in xs (LDS): 19 column
+// blocks over the eight waves, the next block's weights in flight.
+__device__ __forceinline__ void qkv_rows(const float* xs, const float* __restrict__ w, const float* __restrict__ bias,
+                                         float* __restrict__ qkv, int row0) {
+    constexpr int NB = (3 * D + 15) / 16, NW = ROW_T / 64;
+    const int wave = threadIdx.x >> 6, tok = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    Frag<D> xf, wf[2];
+    frag_row(wf[0], w + min(16 * wave + tok, 3 * D - 1) * D, g);
+    frag_row(xf, xs + tok * D, g);
+#pragma unroll
+    for (int i = 0; i < (NB + NW - 1) / NW; ++i) {
+        const int nb = wave + NW * i;
+        if (nb >= NB) break;
+        if (nb + NW < NB) frag_row(wf[(i + 1) & 1], w + min(16 * (nb + NW) + tok, 3 * D - 1) * D, g);
+        const int n = 16 * nb + 4 * g;
+        f32x4 c = mma(wf[i & 1], xf);
+        if (n < 3 * D) {
+            c += ld4(bias + n);
+            st4(qkv + (int64_t)(row0 + tok) * 3 * D + n, c);
+        }
+    }
+}
+
+// The first layer's QKV projection of the batch as sent.
+__global__ void __launch_bounds__(ROW_T) tf_qkv0(const StepIn* __restrict__ in, const Blk* __restrict__ blk,
+                                                 const int* __restrict__ nblk, const float* __restrict__ w,
+                                                 const float* __restrict__ bias, float* __restrict__ qkv) {
+    __shared__ __attribute__((aligned(16))) float sx[BR * D];
+    if ((int)blockIdx.x >= *nblk) return;
+    const Blk q = blk[blockIdx.x];
+    if (threadIdx.x < BR * D / 4) st4(sx + 4 * threadIdx.x, batch4(in, q, threadIdx.x));
+    lds_barrier();
+    qkv_rows(sx, w, bias, qkv, q.row0);
+}
+
+struct RowFwd {
+    const Blk* blk;
+    const int* nblk;
+    const StepIn* in;  // the first layer's residual is the batch
+    const float* x;    // else the layer below's output
+    LayerW w;
+    LayerA a;
+    const float *wqkv_next, *bqkv_next;  // NULL in the last layer
+    float* qkv_next;
+    float scale;
+    int top;
 };
 
-constexpr int kMaxSlices = 16;
-// column sums per layer in the backward: the biases of the four products and
-// the two norms' gain and shift
-constexpr int kLayerSums = 8;
+// What bounds it: a block's 1,000 MFMAs (32 cycles each on four SIMDs: 3.4 us)
+// behind six dependent phases; the chip is not full (one block per 16 valid
+// rows), so a shorter chain matters and not more of them.  The weights of a
+// phase are loaded before the barrier that ends the one before.
+template <int DH>
+__global__ void __launch_bounds__(ROW_T) tf_row_fwd(const RowFwd p) {
+    __shared__ __attribute__((aligned(16))) float sa[BR * D], sx[BR * D], su[BR * D], sh[BR * D];
+    if ((int)blockIdx.x >= *p.nblk) return;
+    const Blk q = p.blk[blockIdx.x];
+    if (p.top && q.r0 > 0) return;
+    const int tid = threadIdx.x, wave = tid >> 6, tok = tid & 15, g = (tid >> 4) & 3;
+    const int n = 16 * wave + 4 * g;                              // the lane's four columns of a d = 100 product
+    const int wr = min(16 * wave + tok, D - 1);                   // the lane's weight row
+    const bool has = n < D;
+    const int64_t row = (int64_t)(q.row0 + tok) * D + n;
+    Frag<D> wf, xf;
+    frag_row(wf, p.w.wo + wr * D, g);
+    if (tid < BR * D / 4)
+        st4(sx + 4 * tid, p.x ? ld4(p.x + (int64_t)q.row0 * D + 4 * tid) : batch4(p.in, q, tid));
+    const LnParam n1 = ln_param(p.w.g1, p.w.b1n), n2 = ln_param(p.w.g2, p.w.b2n);
+    if constexpr (DH == W20) {
+        if (wave < H20) att20_fwd(p.a.qkv, q, wave, p.scale * LOG2E, sa, p.a.O, p.a.lse);
+    } else {
+        load_block(sa, p.a.O + (int64_t)q.row0 * D);
+    }
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 bo = has ? ld4(p.w.bo + n) : zero, b1 = has ? ld4(p.w.b1 + n) : zero, b2 = has ? ld4(p.w.b2 + n) : zero;
+    lds_barrier();
+    frag_row(xf, sa + tok * D, g);
+    f32x4 c = mma(wf, xf);
+    if (has) st4(su + tok * D + n, c + bo + ld4(sx + tok * D + n));
+    frag_row(wf, p.w.w1 + wr * D, g);
+    lds_barrier();
+    ln_fwd(su, n1, sh, p.a.h1, p.a.xh1, p.a.rs1, q.row0);
+    lds_barrier();
+    frag_row(xf, sh + tok * D, g);
+    c = mma(wf, xf) + b1;
+    if (has) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = fmaxf(c[i], 0.f);
+        st4(sa + tok * D + n, c);
+        st4(p.a.f + row, c);
+    }
+    frag_row(wf, p.w.w2 + wr * D, g);
+    lds_barrier();
+    frag_row(xf, sa + tok * D, g);
+    c = mma(wf, xf);
+    if (has) st4(su + tok * D + n, c + b2 + ld4(sh + tok * D + n));
+    lds_barrier();
+    ln_fwd(su, n2, sx, p.a.y, p.a.xh2, p.a.rs2, q.row0);
+    if (!p.wqkv_next) return;
+    lds_barrier();
+    qkv_rows(sx, p.wqkv_next, p.bqkv_next, p.qkv_next, q.row0);
+}
 
-// K slices of a weight gradient (K = the R packed rows)
-int wgrad_slices(int64_t R) { return (int)std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, R / 256)); }
-// Floats of a layer's weight-gradient slices (its four products, each rounded
-// up to 64 floats), kept until the step sums them all before the update.
-size_t layer_wgrad_part(int64_t R) {
-    const int S = wgrad_slices(R);
-    if (S <= 1) return 0;
-    auto r64 = [](size_t n) { return (n + 63) / 64 * 64; };
-    return r64((size_t)S * D * FF) + r64((size_t)S * FF * D) + r64((size_t)S * D * D) + r64((size_t)S * 3 * D * D);
+// ------------------------------------------------------------------ classifier and loss
+// z[b] = Wc y[b, 0] + bc, mean cross-entropy (labels outside [0, 2) clamped and
+// counted), dz, and the classifier's gradients.  One workgroup.
+__global__ void __launch_bounds__(1024) tf_head(const float* __restrict__ y, int64_t ldb, const float* __restrict__ wc,
+                                                const float* __restrict__ bc, const StepIn* __restrict__ in, int B,
+                                                float* __restrict__ logits, float* __restrict__ dz,
+                                                float* __restrict__ gwc, float* __restrict__ gbc,
+                                                float* __restrict__ loss) {
+    constexpr int NW = 16, SP = 5;
+    __shared__ float part[NW], red[SP][NCLS * D];
+    __shared__ int badw[NW];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    float mine = 0.f;
+    int bad = 0;
+    const int l2 = min(lane + 64, D - 1);
+    const float on2 = lane + 64 < D ? 1.f : 0.f;
+    const float w00 = wc[lane], w01 = wc[l2] * on2, w10 = wc[D + lane], w11 = wc[D + l2] * on2, c0 = bc[0], c1 = bc[1];
+    for (int b = w; b < B; b += NW) {
+        const float y0 = y[b * ldb + lane], y1 = y[b * ldb + l2];
+        float z0 = fmaf(y0, w00, y1 * w01), z1 = fmaf(y0, w10, y1 * w11);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            z0 += __shfl_xor(z0, o);
+            z1 += __shfl_xor(z1, o);
+        }
+        z0 += c0;
+        z1 += c1;
+        const float m = fmaxf(z0, z1), lse = m + logf(expf(z0 - m) + expf(z1 - m));
+        int k = in->labels[b];
+        if (k < 0 || k >= NCLS) {
+            bad++;
+            k = k < 0 ? 0 : NCLS - 1;
+        }
+        mine += lse - (k ? z1 : z0);
+        if (lane == 0) {
+            logits[2 * b] = z0;
+            logits[2 * b + 1] = z1;
+            dz[2 * b] = (expf(z0 - lse) - (k == 0 ? 1.f : 0.f)) / (float)B;
+            dz[2 * b + 1] = (expf(z1 - lse) - (k == 1 ? 1.f : 0.f)) / (float)B;
+        }
+    }
+    if (lane == 0) {
+        part[w] = mine;
+        badw[w] = bad;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        float t = 0.f;
+        int nb = 0;
+        for (int i = 0; i < NW; ++i) {
+            t += part[i];
+            nb += badw[i];
+        }
+        loss[0] = t / (float)B;
+        loss[1] = (float)nb;
+    }
+    // dWc[c][k] = sum_b dz[b][c] y[b, 0, k], five interleaved shares of the batch
+    if (tid < SP * NCLS * D) {
+        const int e = tid % (NCLS * D), c = e / D, k = e % D;
+        float s = 0.f;
+#pragma unroll 4
+        for (int b = tid / (NCLS * D); b < B; b += SP) s = fmaf(dz[2 * b + c], y[b * ldb + k], s);
+        red[tid / (NCLS * D)][e] = s;
+    }
+    __syncthreads();
+    if (tid < NCLS * D) gwc[tid] = ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid])) + red[4][tid];
+    if (w == 8 || w == 9) {
+        float s = 0.f;
+        for (int b = lane; b < B; b += 64) s += dz[2 * b + w - 8];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) gbc[w - 8] = s;
+    }
+}
+
+// ------------------------------------------------------------------ a layer's rows, backward
+struct RowBwd {
+    const Blk* blk;
+    const int* nblk;
+    // the gradient of the layer's output: from the layer above (its dqkv, QKV
+    // weights and the residual's du1), or in the last layer from dz and the classifier
+    float* dqkv_up;
+    const float *wqkv_up, *du1_up;
+    const float *qkv_up, *lse_up, *dO_up, *D_up;  // heads of width 20: the attention above runs here
+    const float *dz, *wc;
+    LayerW w;
+    LayerA a;
+    float *du2, *df, *du1, *dO, *Dv, *lnpart;
+    float scale;
+    int heads, top, up_top;
+};
+
+template <int DH>
+__global__ void __launch_bounds__(ROW_T) tf_row_bwd(const RowBwd p) {
+    __shared__ __attribute__((aligned(16))) float sq[BR * 3 * D], sy[BR * D], sd[BR * D], sx[BR * D], st[BR * D];
+    if ((int)blockIdx.x >= *p.nblk) return;
+    const Blk q = p.blk[blockIdx.x];
+    float* part = p.lnpart + (int64_t)blockIdx.x * 4 * D;
+    if (p.top && q.r0 > 0) {  // no gradient reaches these rows of the last layer
+        if (threadIdx.x < 4 * D) part[threadIdx.x] = 0.f;
+        return;
+    }
+    const int tid = threadIdx.x, wave = tid >> 6, tok = tid & 15, g = (tid >> 4) & 3;
+    const int n = 16 * wave + 4 * g, wc = min(16 * wave + tok, D - 1);
+    const bool has = n < D;
+    const int64_t row = (int64_t)(q.row0 + tok) * D + n;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const LnParam n1 = ln_param(p.w.g1, nullptr), n2 = ln_param(p.w.g2, nullptr);
+    const LnSaved s2 = ln_saved(p.a.xh2, p.a.rs2, q.row0);
+    Frag<D> wf, xf;
+    f32x4 c;
+    if (p.top) {
+        if (has) {
+            c = zero;
+            if (tok == 0) {
+                const float z0 = p.dz[2 * q.b], z1 = p.dz[2 * q.b + 1];
+                const f32x4 a = ld4(p.wc + n), b = ld4(p.wc + D + n);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[i] = fmaf(z0, a[i], z1 * b[i]);
+            }
+            st4(sy + tok * D + n, c);
+        }
+    } else {
+        const bool res = has && !(p.up_top && q.r0 > 0);
+        if constexpr (DH == W20) {
+            att20_bwd(p.qkv_up, p.dO_up, p.lse_up, p.D_up, q, p.up_top ? 1 : q.len, p.scale, sq, p.dqkv_up);
+        } else {
+            for (int e = tid; e < BR * 3 * D / 4; e += ROW_T)
+                st4(sq + 4 * e, ld4(p.dqkv_up + (int64_t)q.row0 * 3 * D + 4 * e));
+            lds_barrier();
+        }
+        const f32x4 du1 = res ? ld4(p.du1_up + row) : zero;
+        Frag<3 * D> wq, dq;
+        frag_col(wq, p.wqkv_up + wc, D, g);
+        frag_row(dq, sq + tok * 3 * D, g);
+        c = mma(wq, dq) + du1;
+        if (has) st4(sy + tok * D + n, c);
+    }
+    frag_col(wf, p.w.w2 + wc, FF, g);
+    lds_barrier();
+    // LN2, FFN2, FFN1 (ReLU mask from the stored activation), residual
+    ln_bwd(sy, s2, n2, sx, sd, p.du2, q.row0);
+    const f32x4 f = has ? ld4(p.a.f + row) : zero;
+    lds_barrier();
+    ln_cols(sy, sx, part);
+    frag_row(xf, sd + tok * D, g);
+    c = mma(wf, xf);
+    if (has) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = f[i] > 0.f ? c[i] : 0.f;
+        st4(st + tok * D + n, c);
+        st4(p.df + row, c);
+    }
+    frag_col(wf, p.w.w1 + wc, D, g);
+    const LnSaved s1 = ln_saved(p.a.xh1, p.a.rs1, q.row0);
+    lds_barrier();
+    frag_row(xf, st + tok * D, g);
+    c = mma(wf, xf);
+    if (has) st4(sy + tok * D + n, c + ld4(sd + tok * D + n));
+    frag_col(wf, p.w.wo + wc, D, g);
+    lds_barrier();
+    // LN1, output projection
+    ln_bwd(sy, s1, n1, sx, sd, p.du1, q.row0);
+    const f32x4 o = has ? ld4(p.a.O + row) : zero;
+    lds_barrier();
+    ln_cols(sy, sx, part + 2 * D);
+    frag_row(xf, sd + tok * D, g);
+    c = mma(wf, xf);
+    if (has) {
+        st4(p.dO + row, c);
+        st4(st + tok * D + n, c * o);
+    }
+    lds_barrier();
+    // D = dO . O per row and head
+    for (int e = tid; e < BR * p.heads; e += ROW_T) {
+        const int r = e / p.heads, h = e % p.heads;
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < DH; ++i) s += st[r * D + h * DH + i];
+        p.Dv[(int64_t)(q.row0 + r) * p.heads + h] = s;
+    }
+}
+
+// The first layer's attention backward with heads of width 20 (nothing above it is left to do).
+__global__ void __launch_bounds__(ROW_T) tf_att20_bwd(const Blk* __restrict__ blk, const int* __restrict__ nblk,
+                                                      const float* __restrict__ qkv, const float* __restrict__ dO,
+                                                      const float* __restrict__ lse, const float* __restrict__ Dv,
+                                                      int top, float scale, float* __restrict__ dqkv) {
+    __shared__ __attribute__((aligned(16))) float sq[BR * 3 * D];
+    if ((int)blockIdx.x >= *nblk) return;
+    const Blk q = blk[blockIdx.x];
+    att20_bwd(qkv, dO, lse, Dv, q, top ? 1 : q.len, scale, sq, dqkv);
+}
+
+// ------------------------------------------------------------------ weight gradients
+// Six 100 x 100 products per layer (query, key and value rows of the input
+// projection, output projection, FFN1, FFN2): dW[n][k] = sum over rows of
+// dY[row][n] X[row][k], with a column of ones beside X whose product is the
+// bias gradient.  A workgroup holds a whole product (7 x 7 tiles, one column of
+// tiles per wave) over its share of the row blocks, staged through two LDS
+// buffers with the next block's loads in flight; the shares are added in order
+// by tf_finish.
+constexpr int UNITS = 6, WG_T = 448, LDT = 112;  // 112: the four k rows of a fragment read in distinct banks
+constexpr int LDP = 104;                         // a partial row: 100 weights, the bias, padding
+constexpr int WG_SHARES = 7;  // shares: 12 layers x 6 x 7 = 504 workgroups, two per CU
+
+struct WgradP {
+    const Blk* blk;
+    const int* nblk;
+    const StepIn* in;
+    const float *dqkv, *du1, *df, *du2;  // [layers][rows][300 or 100]
+    const float *y, *O, *h1, *f;         // [layers][rows][100]
+    int64_t rows;                        // rows of a layer's array
+    int layers, shares;
+    float* part;  // [layers][UNITS][shares][100][LDP]
+};
+
+__global__ void __launch_bounds__(WG_T) tf_wgrad(const WgradP p) {
+    __shared__ __attribute__((aligned(16))) float sm[2][2][BR * LDT];
+    const int tid = threadIdx.x, wave = tid >> 6, tok = tid & 15, g = (tid >> 4) & 3;
+    const int share = blockIdx.x % p.shares, unit = blockIdx.x / p.shares % UNITS;
+    const int layer = blockIdx.x / p.shares / UNITS;
+    const int64_t lr = (int64_t)layer * p.rows;
+    const float *dy, *x;
+    int ldy = D;
+    switch (unit) {
+        case 3: dy = p.du1 + lr * D; x = p.O + lr * D; break;
+        case 4: dy = p.df + lr * D; x = p.h1 + lr * D; break;
+        case 5: dy = p.du2 + lr * D; x = p.f + lr * D; break;
+        default:
+            dy = p.dqkv + lr * 3 * D + unit * D;
+            ldy = 3 * D;
+            x = layer ? p.y + (lr - p.rows) * D : nullptr;  // NULL: the batch as sent
+    }
+    // the last layer past its attention: only the first token's block was computed
+    const bool first_only = layer == p.layers - 1 && unit >= 3;
+    const int nb = *p.nblk;
+    auto next = [&](int i) {  // the share's next block from i on
+        while (first_only && i < nb && p.blk[i].r0 > 0) i += p.shares;
+        return i;
+    };
+    // element groups of a staged block: 400 of dY, 400 of X, two per thread
+    f32x4 r[2];
+    auto load = [&](int i) {
+        const Blk q = p.blk[i];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = tid + u * WG_T;
+            if (e >= 800) break;
+            const int e2 = e % 400, row = e2 / 25, c = e2 % 25 * 4;
+            if (e < 400)
+                r[u] = ld4(dy + (int64_t)(q.row0 + row) * ldy + c);
+            else
+                r[u] = x ? ld4(x + (int64_t)(q.row0 + row) * D + c) : batch4(p.in, q, e2);
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int e = tid + u * WG_T;
+            if (e >= 800) break;
+            const int e2 = e % 400;
+            st4(&sm[buf][e / 400][e2 / 25 * LDT + e2 % 25 * 4], r[u]);
+        }
+    };
+    for (int e = tid; e < 4 * BR * 12; e += WG_T) {  // the columns past 100: zeros, and the column of ones
+        const int c = e % 12, row = e / 12 % BR, b = e / 12 / BR;
+        sm[b >> 1][b & 1][row * LDT + D + c] = (b & 1) && c == 0 ? 1.f : 0.f;
+    }
+    f32x4 acc[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int i = next(share), buf = 0;
+    if (i < nb) {
+        load(i);
+        store(0);
+    }
+    lds_barrier();
+    while (i < nb) {
+        const int j = next(i + p.shares);
+        if (j < nb) load(j);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float b = sm[buf][0][(4 * s + g) * LDT + 16 * wave + tok];
+#pragma unroll
+            for (int k = 0; k < 7; ++k) acc[k] = mfma(sm[buf][1][(4 * s + g) * LDT + 16 * k + tok], b, acc[k]);
+        }
+        if (j < nb) store(buf ^ 1);
+        lds_barrier();
+        buf ^= 1;
+        i = j;
+    }
+    const int n = 16 * wave + tok;
+    if (n >= D) return;
+    float* o = p.part + ((int64_t)blockIdx.x * D + n) * LDP;
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+        if (16 * k + 4 * g < LDP) st4(o + 16 * k + 4 * g, acc[k]);
+}
+
+// ------------------------------------------------------------------ gradients and update
+// Adds the shares of the weight and bias gradients and the blocks' shares of
+// the norms' gradients, stores the gradient and updates the parameter
+// (theta <- theta - lr g).  Workgroups: per layer UNITS x FIN_SPLIT for the
+// products (20 rows each), 4 for the norms, and one for the classifier.
+constexpr int FIN_SPLIT = 5, FIN_ROWS = D / FIN_SPLIT, FIN_LAYER = UNITS * FIN_SPLIT + 4, FIN_T = 1024;
+constexpr int64_t kLayer = 3LL * D * D + 3 * D + (int64_t)D * D + D + 2 * D + (int64_t)FF * D + FF + (int64_t)D * FF +
+                           D + 2 * D;
+// offsets of a layer's parameters
+constexpr int oWqkv = 0, oBqkv = oWqkv + 3 * D * D, oWo = oBqkv + 3 * D, oBo = oWo + D * D, oG1 = oBo + D,
+              oB1n = oG1 + D, oW1 = oB1n + D, oB1 = oW1 + FF * D, oW2 = oB1 + FF, oB2 = oW2 + D * FF, oG2 = oB2 + D,
+              oB2n = oG2 + D;
+static_assert(oB2n + D == kLayer, "layer layout");
+static_assert(D == FF, "every product is d x d");
+
+__device__ __forceinline__ void update(float* prm, float* grd, int64_t i, float v, float lr) {
+    grd[i] = v;
+    prm[i] = __builtin_fmaf(-lr, v, prm[i]);
+}
+
+__global__ void __launch_bounds__(FIN_T) tf_finish(const float* __restrict__ part, int shares,
+                                                   const float* __restrict__ lnpart, int64_t lnstride,
+                                                   const int* __restrict__ nblk, int layers, float* __restrict__ prm,
+                                                   float* __restrict__ grd, float lr) {
+    constexpr int SP = 8;
+    __shared__ float red[SP][D];
+    const int layer = blockIdx.x / FIN_LAYER, job = blockIdx.x % FIN_LAYER, tid = threadIdx.x;
+    const int64_t base = layer * kLayer;
+    if (layer >= layers) {  // the classifier's gradient is complete
+        if (tid < NCLS * D + NCLS) prm[base + tid] = __builtin_fmaf(-lr, grd[base + tid], prm[base + tid]);
+        return;
+    }
+    if (job < UNITS * FIN_SPLIT) {
+        const int unit = job / FIN_SPLIT, n0 = job % FIN_SPLIT * FIN_ROWS;
+        const int n = n0 + tid / 26, c = tid % 26 * 4;  // 25 groups of four weights, then the bias
+        if (tid >= FIN_ROWS * 26) return;
+        constexpr int ow[UNITS] = {oWqkv, oWqkv + D * D, oWqkv + 2 * D * D, oWo, oW1, oW2};
+        constexpr int ob[UNITS] = {oBqkv, oBqkv + D, oBqkv + 2 * D, oBo, oB1, oB2};
+        const float* s = part + (((int64_t)layer * UNITS + unit) * shares * D + n) * LDP + c;
+        f32x4 v = ld4(s);
+        int z = 1;
+        for (; z + 2 < shares; z += 3) {
+            const f32x4 a = ld4(s + (int64_t)z * D * LDP), b = ld4(s + (int64_t)(z + 1) * D * LDP),
+                        d = ld4(s + (int64_t)(z + 2) * D * LDP);
+            v += a;
+            v += b;
+            v += d;
+        }
+        for (; z < shares; ++z) v += ld4(s + (int64_t)z * D * LDP);
+        if (c < D) {
+            const int64_t i = base + ow[unit] + n * D + c;
+            f32x4 t = ld4(prm + i);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t[k] = __builtin_fmaf(-lr, v[k], t[k]);
+            st4(grd + i, v);
+            st4(prm + i, t);
+        } else {
+            update(prm, grd, base + ob[unit] + n, v[0], lr);
+        }
+        return;
+    }
+    const int which = job - UNITS * FIN_SPLIT;  // gamma2, beta2, gamma1, beta1
+    const int c = tid % D, sp = tid / D;
+    if (sp < SP) {
+        const float* s = lnpart + layer * lnstride + which * D + c;
+        const int nb = *nblk;
+        float v = 0.f;
+        int b = sp;
+        for (; b + 3 * SP < nb; b += 4 * SP) {
+            const float a0 = s[(int64_t)b * 4 * D], a1 = s[(int64_t)(b + SP) * 4 * D],
+                        a2 = s[(int64_t)(b + 2 * SP) * 4 * D], a3 = s[(int64_t)(b + 3 * SP) * 4 * D];
+            v += (a0 + a1) + (a2 + a3);
+        }
+        for (; b < nb; b += SP) v += s[(int64_t)b * 4 * D];
+        red[sp][c] = v;
+    }
+    __syncthreads();
+    if (tid >= D) return;
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < SP; ++k) v += red[k][tid];
+    const int off = which == 0 ? oG2 : which == 1 ? oB2n : which == 2 ? oG1 : oB1n;
+    update(prm, grd, base + off + tid, v, lr);
+}
+
+// ------------------------------------------------------------------ plan
+struct Plan {
+    Arch a;
+    int64_t rows;  // max_batch * L
+    int* nblk;
+    Blk* blk;
+    // saved activations and gradients, one array per kind over all layers
+    float *qkv, *O, *lse, *xh1, *rs1, *h1, *f, *xh2, *rs2, *y;
+    float *dqkv, *du1, *df, *du2, *dO, *Dv, *lnpart, *dz, *part;
+};
+
+// Carves the plan from the arena; with base == NULL it only counts the bytes.
+size_t carve(Plan* P, const fo_model* m, Arena* ar) {
+    const Arch a = arch_of(m->cid);
+    const size_t R = (size_t)m->max_batch * a.L, nl = a.layers, NB = R / BR;
+    size_t s = 0;
+    auto take = [&](auto*& p, size_t n) {
+        using T = std::remove_reference_t<decltype(*p)>;
+        s += (n * sizeof(T) + 255) & ~size_t(255);
+        if (ar) p = ar->template take<T>(n);
+    };
+    P->a = a;
+    P->rows = (int64_t)R;
+    take(P->nblk, 1);
+    take(P->blk, NB);
+    take(P->qkv, nl * R * 3 * D);
+    for (float** b : {&P->O, &P->xh1, &P->h1, &P->f, &P->xh2, &P->y, &P->du1, &P->df, &P->du2}) take(*b, nl * R * D);
+    for (float** b : {&P->rs1, &P->rs2}) take(*b, nl * R);
+    take(P->lse, nl * R * a.heads);
+    take(P->dqkv, nl * R * 3 * D);
+    take(P->dO, R * D * 2);
+    take(P->Dv, R * a.heads * 2);
+    take(P->lnpart, nl * NB * 4 * D);
+    take(P->dz, (size_t)m->max_batch * NCLS);
+    take(P->part, nl * UNITS * WG_SHARES * D * LDP);
+    return s;
 }
 
 size_t ws_bytes(const fo_model* m) {
-    const Arch a = arch_of(m->cid);
-    const size_t R = (size_t)m->max_batch * a.L, Bm = m->max_batch;
-    size_t s = 0;
-    auto add = [&](size_t b) { s += (b + 255) & ~size_t(255); };
-    add(sizeof(Plan));
-    for (int l = 0; l < a.layers; ++l) {
-        add(4 * R * 3 * D);              // qkv
-        add(4 * R * D);                  // O
-        add(4 * Bm * a.heads * a.L);     // lse
-        add(4 * R * D);                  // xh1
-        add(4 * R);                      // rs1
-        add(4 * R * D);                  // h1
-        add(4 * R * FF);                 // f
-        add(4 * R * D);                  // xh2
-        add(4 * R);                      // rs2
-        add(4 * R * D);                  // y
-    }
-    add(4 * Bm * NCLS);                                               // dz
-    for (int i = 0; i < 8; ++i) add(4 * R * 3 * D);                   // dy, du2, df, dh1, du1, dO, dqkv, dx (+gx)
-    add(4 * R * D);                                                   // gx
-    add(4 * R * D);                                                   // gx1
-    add(4 * (size_t)kMaxSlices * 3 * D * D);                          // part
-    add(4 * colsum_ws_floats((int)R, 3 * D));                         // colws
-    add(4 * kLayerSums * colsum_ws_floats((int)R, 3 * D));            // sumws
-    add(4 * a.layers * layer_wgrad_part((int64_t)R));                 // wgpart
-    return s;
+    Plan P;
+    return carve(&P, m, nullptr);
 }
 
 fo_status init(fo_model* m) {
     Plan* P = new (std::nothrow) Plan();
     if (!P) return FO_ENOMEM;
     m->plan = P;
-    P->a = arch_of(m->cid);
-    P->ly = new (std::nothrow) LayerP[P->a.layers];
-    if (!P->ly) return FO_ENOMEM;
-    const size_t R = (size_t)m->max_batch * P->a.L, Bm = m->max_batch;
-    const float* p = m->params;
-    float* g = m->grads;
-    auto take = [&](const float*& w, float*& gw, size_t n) {
-        w = p;
-        gw = g;
-        p += n;
-        g += n;
-    };
-    Arena& ar = m->arena;
-    ar.take<char>(sizeof(Plan));
-    for (int l = 0; l < P->a.layers; ++l) {
-        LayerP& L = P->ly[l];
-        take(L.wqkv, L.gwqkv, 3 * D * D);
-        take(L.bqkv, L.gbqkv, 3 * D);
-        take(L.wo, L.gwo, D * D);
-        take(L.bo, L.gbo, D);
-        take(L.g1, L.gg1, D);
-        take(L.b1n, L.gb1n, D);
-        take(L.w1, L.gw1, FF * D);
-        take(L.b1, L.gb1, FF);
-        take(L.w2, L.gw2, D * FF);
-        take(L.b2, L.gb2, D);
-        take(L.g2, L.gg2, D);
-        take(L.b2n, L.gb2n, D);
-        L.qkv = ar.take<float>(R * 3 * D);
-        L.O = ar.take<float>(R * D);
-        L.lse = ar.take<float>(Bm * P->a.heads * P->a.L);
-        L.xh1 = ar.take<float>(R * D);
-        L.rs1 = ar.take<float>(R);
-        L.h1 = ar.take<float>(R * D);
-        L.f = ar.take<float>(R * FF);
-        L.xh2 = ar.take<float>(R * D);
-        L.rs2 = ar.take<float>(R);
-        L.y = ar.take<float>(R * D);
-    }
-    take(P->wc, P->gwc, NCLS * D);
-    take(P->bc, P->gbc, NCLS);
-    P->dz = ar.take<float>(Bm * NCLS);
-    float** bufs[8] = {&P->dy, &P->du2, &P->df, &P->dh1, &P->du1, &P->dO, &P->dqkv, &P->dx};
-    for (float** b : bufs) *b = ar.take<float>(R * 3 * D);
-    P->gx = ar.take<float>(R * D);
-    P->gx1 = ar.take<float>(R * D);
-    P->part_floats = (size_t)kMaxSlices * 3 * D * D;
-    P->part = ar.take<float>(P->part_floats);
-    P->colws = ar.take<float>(colsum_ws_floats((int)R, 3 * D));
-    P->sumws = ar.take<float>(kLayerSums * colsum_ws_floats((int)R, 3 * D));
-    P->wgpart = ar.take<float>(std::max<size_t>(1, P->a.layers * layer_wgrad_part((int64_t)R)));
-    if (!P->wgpart) {
+    carve(P, m, &m->arena);
+    if (!P->part) {
         set_error("tfsmall: workspace arena too small");
         return FO_ENOMEM;
     }
     return FO_OK;
 }
 
-struct Ctx {
-    hipStream_t s;
-    Plan* P;
-};
-
-// C = epi(sum_k A(m, k) B(n, k)) (see GemmF32); S slices over K for long reductions.
-fo_status gemm(const Ctx& c, const Gf& g) { return launch_gemm_f32(g, c.P->part, c.P->part_floats, c.s); }
-
-Gf prod(const float* A, int64_t am, int64_t ak, const float* B, int64_t bn, int64_t bk, float* C, int64_t ldc, int M,
-        int N, int K) {
-    Gf g{};
-    g.A = A;
-    g.am = am;
-    g.ak = ak;
-    g.B = B;
-    g.bn = bn;
-    g.bk = bk;
-    g.C = C;
-    g.ldc = ldc;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.S = 1;
-    return g;
-}
-
-// y[r][n] = x[r][:] . W[n][:] + b[n] (+ add[r][n], ReLU), W [N][K]
-Gf linear(const float* x, const StepIn* inx, const float* W, const float* b, float* y, int R, int N, int K) {
-    Gf g = prod(x, K, 1, W, K, 1, y, N, R, N, K);
-    g.inA = inx;
-    g.bias = b;
-    return g;
-}
-// dx[r][k] = dy[r][:] . W[:][k] (+ add), W [N][K]
-Gf linear_dx(const float* dy, const float* W, float* dx, int R, int N, int K) {
-    return prod(dy, N, 1, W, 1, K, dx, K, R, K, N);
-}
-// dW[n][k] = sum_r dy[r][n] x[r][k] (x = the batch when inx is set).  Nothing
-// reads dW before the update, so its K slices stay at *part (which advances)
-// and join `sums`, added up for every layer in one launch at the end of the
-// backward instead of one reduction launch per product.
-fo_status linear_dw(const Ctx& c, const float* dy, const float* x, const StepIn* inx, float* dW, int R, int N, int K,
-                    SplitJobs& sums, float*& part) {
-    Gf g = prod(dy, 1, N, x, 1, K, dW, K, N, K, R);
-    g.inB = inx;
-    g.S = wgrad_slices(R);
-    if (g.S <= 1) return gemm(c, g);
-    FO_CHECK(sums.n < kSplitJobsMax, "tfsmall: more than %d deferred weight-gradient sums", kSplitJobsMax);
-    g.defer = 1;
-    const size_t n = (size_t)g.S * N * K;
-    SplitJob& j = sums.j[sums.n++];
-    j.ws = part; j.C = dW; j.ldc = K; j.S = g.S; j.M = N; j.N = K;
-    const fo_status st = launch_gemm_f32(g, part, n, c.s);
-    part += (n + 63) / 64 * 64;
-    return st;
-}
-fo_status colsum(const Ctx& c, const float* X, int R, int N, float* out) {
-    return launch_colsum(X, N, R, nullptr, N, out, c.P->colws, c.s);
+template <int DH>
+fo_status run(fo_model* m, int B) {
+    const Plan* P = (const Plan*)m->plan;
+    const Arch a = P->a;
+    const int NB = B * a.L / BR, top = a.layers - 1;
+    const float scale = 1.f / sqrtf((float)DH);
+    const int64_t R = P->rows;
+    hipStream_t s = m->stream;
+    const float* prm = m->params;
+    auto weights = [&](int l) {
+        const float* p = prm + l * kLayer;
+        return LayerW{p + oWqkv, p + oBqkv, p + oWo, p + oBo, p + oG1, p + oB1n,
+                      p + oW1,   p + oB1,   p + oW2, p + oB2, p + oG2, p + oB2n};
+    };
+    auto saved = [&](int l) {
+        const int64_t r = l * R;
+        return LayerA{P->qkv + r * 3 * D, P->O + r * D, P->lse + r * a.heads, P->xh1 + r * D, P->rs1 + r,
+                      P->h1 + r * D,      P->f + r * D, P->xh2 + r * D,       P->rs2 + r,     P->y + r * D};
+    };
+    const float* wc = prm + a.layers * kLayer;
+    hipLaunchKernelGGL(tf_setup, dim3(1), dim3(1024), sizeof(int) * B, s, m->dev_in, B, a.L, P->blk, P->nblk,
+                       m->loss + 2);
+    // forward (Alg. 4: forward pass of M_s)
+    hipLaunchKernelGGL(tf_qkv0, dim3(NB), dim3(ROW_T), 0, s, m->dev_in, P->blk, P->nblk, prm + oWqkv, prm + oBqkv,
+                       P->qkv);
+    for (int l = 0; l < a.layers; ++l) {
+        RowFwd p{};
+        p.blk = P->blk;
+        p.nblk = P->nblk;
+        p.in = m->dev_in;
+        p.x = l ? P->y + (l - 1) * R * D : nullptr;
+        p.w = weights(l);
+        p.a = saved(l);
+        if (l < top) {
+            const LayerW wn = weights(l + 1);
+            p.wqkv_next = wn.wqkv;
+            p.bqkv_next = wn.bqkv;
+            p.qkv_next = saved(l + 1).qkv;
+        }
+        p.scale = scale;
+        p.top = l == top;
+        if (DH == 2) {
+            hipLaunchKernelGGL(att2_fwd, dim3(2 * NB), dim3(ATT_T), 0, s, p.a.qkv, P->blk, P->nblk, p.top, p.a.O,
+                               p.a.lse, scale);
+        }
+        hipLaunchKernelGGL(tf_row_fwd<DH>, dim3(NB), dim3(ROW_T), 0, s, p);
+    }
+    // classifier on the first token, loss f_s (Eq. 5)
+    float* gwc = m->grads + a.layers * kLayer;
+    hipLaunchKernelGGL(tf_head, dim3(1), dim3(1024), 0, s, P->y + top * R * D, (int64_t)a.L * D, wc, wc + NCLS * D,
+                       m->dev_in, B, m->logits, P->dz, gwc, gwc + NCLS * D, m->loss);
+    FO_LAUNCHED();
+    // backward (Alg. 4: backward pass of M_s)
+    const int64_t lnstride = (int64_t)(R / BR) * 4 * D;
+    for (int l = top; l >= 0; --l) {
+        // two sets of dO and D: with heads of width 20 the launch of layer l reads layer l + 1's
+        float *dO = P->dO + (l & 1) * R * D, *Dv = P->Dv + (l & 1) * R * a.heads;
+        RowBwd p{};
+        p.blk = P->blk;
+        p.nblk = P->nblk;
+        p.dz = P->dz;
+        p.wc = wc;
+        p.w = weights(l);
+        p.a = saved(l);
+        if (l < top) {
+            const LayerA up = saved(l + 1);
+            p.dqkv_up = P->dqkv + (l + 1) * R * 3 * D;
+            p.wqkv_up = weights(l + 1).wqkv;
+            p.du1_up = P->du1 + (l + 1) * R * D;
+            p.qkv_up = up.qkv;
+            p.lse_up = up.lse;
+            p.dO_up = P->dO + ((l + 1) & 1) * R * D;
+            p.D_up = P->Dv + ((l + 1) & 1) * R * a.heads;
+        }
+        p.du2 = P->du2 + l * R * D;
+        p.df = P->df + l * R * D;
+        p.du1 = P->du1 + l * R * D;
+        p.dO = dO;
+        p.Dv = Dv;
+        p.lnpart = P->lnpart + l * lnstride;
+        p.scale = scale;
+        p.heads = a.heads;
+        p.top = l == top;
+        p.up_top = l + 1 == top;
+        hipLaunchKernelGGL(tf_row_bwd<DH>, dim3(NB), dim3(ROW_T), 0, s, p);
+        if (DH == 2)
+            hipLaunchKernelGGL(att2_bwd, dim3(2 * NB, 2), dim3(ATT_T), 0, s, p.a.qkv, dO, p.a.lse, Dv, P->blk, P->nblk,
+                               p.top, P->dqkv + l * R * 3 * D, scale);
+        else if (l == 0)
+            hipLaunchKernelGGL(tf_att20_bwd, dim3(NB), dim3(ROW_T), 0, s, P->blk, P->nblk, p.a.qkv, dO, p.a.lse, Dv,
+                               p.top, scale, P->dqkv);
+    }
+    FO_LAUNCHED();
+    // weight gradients of every layer, then their sums and SGD (Alg. 4)
+    WgradP w{};
+    w.blk = P->blk;
+    w.nblk = P->nblk;
+    w.in = m->dev_in;
+    w.dqkv = P->dqkv;
+    w.du1 = P->du1;
+    w.df = P->df;
+    w.du2 = P->du2;
+    w.y = P->y;
+    w.O = P->O;
+    w.h1 = P->h1;
+    w.f = P->f;
+    w.rows = R;
+    w.layers = a.layers;
+    w.shares = std::min(WG_SHARES, NB);
+    w.part = P->part;
+    hipLaunchKernelGGL(tf_wgrad, dim3(a.layers * UNITS * w.shares), dim3(WG_T), 0, s, w);
+    hipLaunchKernelGGL(tf_finish, dim3(a.layers * FIN_LAYER + 1), dim3(FIN_T), 0, s, P->part, w.shares, P->lnpart,
+                       lnstride, P->nblk, a.layers, m->params, m->grads, m->lr);
+    FO_LAUNCHED();
+    return FO_OK;
 }
 
 fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
     (void)labels;  // read through m->dev_in
-    Plan* P = (Plan*)m->plan;
-    const Arch a = P->a;
-    const int B = acts->batch, L = a.L, R = B * L, H = a.heads, dh = D / H;
-    const float scale = 1.f / sqrtf((float)dh);
-    const Ctx c{m->stream, P};
-    hipStream_t s = m->stream;
-    fo_status st = FO_OK;
-#define TRY(x)                   \
-    do {                         \
-        st = (x);                \
-        if (st != FO_OK) return st; \
-    } while (0)
-    hipLaunchKernelGGL(lengths_check, dim3(1), dim3(64), 0, s, m->dev_in, B, L, m->loss + 2);
-    FO_LAUNCHED();
-    const size_t fwd_lds = sizeof(float) * 2 * L * dh, bwd_lds = sizeof(float) * (2 * L * dh + 2 * L);
-    // forward (Alg. 4: forward pass of M_s)
-    for (int l = 0; l < a.layers; ++l) {
-        LayerP& Y = P->ly[l];
-        const float* x = l ? P->ly[l - 1].y : nullptr;
-        const StepIn* inx = l ? nullptr : m->dev_in;
-        TRY(gemm(c, linear(x, inx, Y.wqkv, Y.bqkv, Y.qkv, R, 3 * D, D)));
-        if (dh == 20)
-            hipLaunchKernelGGL(attn_small_fwd<20>, dim3(B * H), dim3(256), fwd_lds, s, Y.qkv, m->dev_in, Y.O, Y.lse,
-                               H, L, scale);
-        else
-            hipLaunchKernelGGL(attn_small_fwd<2>, dim3(B * H), dim3(256), fwd_lds, s, Y.qkv, m->dev_in, Y.O, Y.lse,
-                               H, L, scale);
-        FO_LAUNCHED();
-        Gf go = linear(Y.O, nullptr, Y.wo, Y.bo, P->dx, R, D, D);  // u1 = x + O Wo^T + bo (into dx as scratch)
-        go.add = x;
-        go.inAdd = inx;
-        go.ldadd = D;
-        TRY(gemm(c, go));
-        hipLaunchKernelGGL(ln_small_fwd, dim3((int)cdiv(R, 4)), dim3(256), 0, s, P->dx, Y.g1, Y.b1n, Y.h1, Y.xh1, Y.rs1,
-                           R);
-        FO_LAUNCHED();
-        Gf g1 = linear(Y.h1, nullptr, Y.w1, Y.b1, Y.f, R, FF, D);
-        g1.relu = 1;
-        TRY(gemm(c, g1));
-        Gf g2 = linear(Y.f, nullptr, Y.w2, Y.b2, P->dx, R, D, FF);  // u2 = h1 + f W2^T + b2
-        g2.add = Y.h1;
-        g2.ldadd = D;
-        TRY(gemm(c, g2));
-        hipLaunchKernelGGL(ln_small_fwd, dim3((int)cdiv(R, 4)), dim3(256), 0, s, P->dx, Y.g2, Y.b2n, Y.y, Y.xh2, Y.rs2,
-                           R);
-        FO_LAUNCHED();
-    }
-    // classifier on the first token, loss f_s (Eq. 5)
-    const float* ytop = P->ly[a.layers - 1].y;
-    Gf gz = prod(ytop, (int64_t)L * D, 1, P->wc, D, 1, m->logits, NCLS, B, NCLS, D);  // rows b at token 0
-    gz.bias = P->bc;
-    TRY(gemm(c, gz));
-    TRY(launch_xent(m->logits, m->dev_in, P->dz, m->loss, B, NCLS, s));
-    // backward (Alg. 4: backward pass of M_s)
-    float* dy = P->dy;  // gradient of the current layer's output
-    float* dx = P->dx;  // gradient of its input
-    // dWc[c][k] = sum_b dz[b][c] y[b, 0, k]; dy[b, 0, :] = dz[b] Wc, zero elsewhere
-    TRY(gemm(c, prod(P->dz, 1, NCLS, ytop, 1, (int64_t)L * D, P->gwc, D, NCLS, D, B)));
-    TRY(colsum(c, P->dz, B, NCLS, P->gbc));
-    TRY(launch_fill(dy, (int64_t)R * D, 0.f, s));
-    TRY(gemm(c, prod(P->dz, NCLS, 1, P->wc, 1, D, dy, (int64_t)L * D, B, D, NCLS)));
-    SplitJobs wsums;
-    float* wpart = P->wgpart;
-    for (int l = a.layers - 1; l >= 0; --l) {
-        LayerP& Y = P->ly[l];
-        const float* x = l ? P->ly[l - 1].y : nullptr;
-        const StepIn* inx = l ? nullptr : m->dev_in;
-        // LN2
-        hipLaunchKernelGGL(ln_small_bwd, dim3((int)cdiv(R, 4)), dim3(256), 0, s, dy, Y.xh2, Y.rs2, Y.g2, P->du2,
-                           P->gx, R);
-        FO_LAUNCHED();
-        // The layer's eight column sums (biases, norm gains and shifts) run as
-        // one pass at the end of the layer, over buffers that stay intact until then.
-        ColSums sums;
-        const size_t sw = colsum_ws_floats(R, 3 * D);
-        auto sum = [&](const float* X, int N, float* out) {
-            sums.add(X, N, R, N, P->sumws + sums.parts.n * sw, out);
-        };
-        sum(P->gx, D, Y.gg2);
-        sum(dy, D, Y.gb2n);
-        // FFN2 and FFN1 (ReLU mask from the stored activation)
-        TRY(linear_dw(c, P->du2, Y.f, nullptr, Y.gw2, R, D, FF, wsums, wpart));
-        sum(P->du2, D, Y.gb2);
-        Gf gdf = linear_dx(P->du2, Y.w2, P->df, R, D, FF);
-        gdf.mask = Y.f;
-        gdf.ldmask = FF;
-        TRY(gemm(c, gdf));
-        TRY(linear_dw(c, P->df, Y.h1, nullptr, Y.gw1, R, FF, D, wsums, wpart));
-        sum(P->df, FF, Y.gb1);
-        Gf gdh = linear_dx(P->df, Y.w1, P->dh1, R, FF, D);  // dh1 = du2 + df W1
-        gdh.add = P->du2;
-        gdh.ldadd = D;
-        TRY(gemm(c, gdh));
-        // LN1
-        hipLaunchKernelGGL(ln_small_bwd, dim3((int)cdiv(R, 4)), dim3(256), 0, s, P->dh1, Y.xh1, Y.rs1, Y.g1, P->du1,
-                           P->gx1, R);
-        FO_LAUNCHED();
-        sum(P->gx1, D, Y.gg1);
-        sum(P->dh1, D, Y.gb1n);
-        // output projection
-        TRY(linear_dw(c, P->du1, Y.O, nullptr, Y.gwo, R, D, D, wsums, wpart));
-        sum(P->du1, D, Y.gbo);
-        TRY(gemm(c, linear_dx(P->du1, Y.wo, P->dO, R, D, D)));
-        // attention
-        if (dh == 20)
-            hipLaunchKernelGGL(attn_small_bwd<20>, dim3(B * H), dim3(256), bwd_lds, s, Y.qkv, m->dev_in, Y.O, P->dO,
-                               Y.lse, P->dqkv, H, L, scale);
-        else
-            hipLaunchKernelGGL(attn_small_bwd<2>, dim3(B * H), dim3(256), bwd_lds, s, Y.qkv, m->dev_in, Y.O, P->dO,
-                               Y.lse, P->dqkv, H, L, scale);
-        FO_LAUNCHED();
-        // QKV projection (no input gradient for the first server layer: nothing is sent back)
-        TRY(linear_dw(c, P->dqkv, x, inx, Y.gwqkv, R, 3 * D, D, wsums, wpart));
-        sum(P->dqkv, 3 * D, Y.gbqkv);
-        TRY(launch_colsums(sums, s));
-        if (l > 0) {
-            Gf gx = linear_dx(P->dqkv, Y.wqkv, dx, R, 3 * D, D);  // dx = du1 + dqkv Wqkv
-            gx.add = P->du1;
-            gx.ldadd = D;
-            TRY(gemm(c, gx));
-            std::swap(dy, dx);
-        }
-    }
-    if (wsums.n) TRY(launch_splitk_sum_multi(wsums, s));
-#undef TRY
-    // SGD (Alg. 4)
-    return launch_sgd(m->params, m->grads, nullptr, nullptr, nullptr, m->n_params, m->lr, 0.f, s);
+    return m->cid == 7 ? run<W20>(m, acts->batch) : run<2>(m, acts->batch);
 }
 
 void destroy(fo_model* m) {
-    Plan* P = (Plan*)m->plan;
-    if (P) delete[] P->ly;
-    delete P;
+    delete (Plan*)m->plan;
     m->plan = nullptr;
 }
 
 }  // namespace
 
-int64_t tfsmall_param_count(int32_t cid) {
-    const Arch a = arch_of(cid);
-    const int64_t per = 3LL * D * D + 3 * D + (int64_t)D * D + D + 2 * D + (int64_t)FF * D + FF + (int64_t)D * FF + D +
-                        2 * D;
-    return a.layers * per + (int64_t)NCLS * D + NCLS;
-}
+int64_t tfsmall_param_count(int32_t cid) { return arch_of(cid).layers * kLayer + (int64_t)NCLS * D + NCLS; }
 
 const Family* family_tfsmall7() {
     static const Family f = {(int64_t)64 * D * 4, ws_bytes, init, step, destroy};

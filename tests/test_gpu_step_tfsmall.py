@@ -97,3 +97,28 @@ def test_lengths_outside_the_sequence_are_reported():
         assert "2 sequence length(s)" in str(e.value)
     finally:
         A.fo_model_destroy(model)
+
+
+# The rows are computed in blocks of 16 of one sequence, and (Transformer-12)
+# halves of a block against eighths of the other side: lengths around their
+# edges, shorter than the eighths, and padded positions that hold NaN (no
+# output may read them).  Bound as above; the batches are seeds without a ReLU
+# input within 1e-5 of zero, where another order of summation could take
+# the other branch.
+@pytest.mark.parametrize("cid,lengths,sub", [(7, [1, 15, 16, 17, 48, 49, 64], 33),
+                                             (8, [8, 9, 16, 17, 31, 33, 255], 44)])
+def test_block_edges(cid, lengths, sub):
+    torch = torch_cuda()
+    B = len(lengths)
+    acts, labels, ln = _batch(cid, B, sub, lengths)
+    announce(f"config {cid} block edges lengths={lengths}")
+    padded = acts.copy()
+    for b in range(B):
+        padded[b, lengths[b]:] = np.nan
+    theta = S.init_params(cid)
+    model = A.fo_model_create(cid, B + 2, theta, torch.cuda.current_stream())
+    try:
+        out = _step(model, to_dev(padded), to_dev(labels), to_dev(ln), B)
+        _check(cid, out, theta.astype(np.float64), acts, labels, ln)
+    finally:
+        A.fo_model_destroy(model)
