@@ -13,33 +13,18 @@
 // depthwise convolution one thread per output (forward) or input (input
 // gradient) and one workgroup per channel for its weight gradient.
 #include "gemm.h"
-#include "model.h"
+#include "mbv3.h"
+#include "small_f32.h"
 
 namespace fo {
 
 namespace {
 
-constexpr int CIN = 80, HIN = 4, CLAST = 960, F1 = 1280, NCLS = 200, NBLK = 8;
-constexpr float BN_EPS = 1e-5f;
+using namespace mbv3;
+
 constexpr int kMaxSlices = 16;
 
-struct Blk {
-    int k, e, co, se, stride;
-};
-constexpr Blk kBlk[NBLK] = {{3, 200, 80, 0, 1}, {3, 184, 80, 0, 1}, {3, 184, 80, 0, 1}, {3, 480, 112, 1, 1},
-                            {3, 672, 112, 1, 1}, {5, 672, 160, 1, 2}, {5, 960, 160, 1, 1}, {5, 960, 160, 1, 1}};
-// squeeze width: e / 4 to a multiple of 8, at least 8, not below 90% of e / 4
-constexpr int se_width(int e) {
-    return (e / 4 + 4) / 8 * 8 < 8 ? 8
-           : ((e / 4 + 4) / 8 * 8 < 0.9 * (e / 4) ? (e / 4 + 4) / 8 * 8 + 8 : (e / 4 + 4) / 8 * 8);
-}
-
 inline int nblk(int64_t n) { return (int)cdiv(n, 256); }
-
-__device__ __forceinline__ float hswish(float x) { return x * fminf(fmaxf(x + 3.f, 0.f), 6.f) * (1.f / 6.f); }
-__device__ __forceinline__ float hswish_d(float x) { return x < -3.f ? 0.f : (x > 3.f ? 1.f : (2.f * x + 3.f) / 6.f); }
-__device__ __forceinline__ float hsig(float x) { return fminf(fmaxf(x + 3.f, 0.f), 6.f) * (1.f / 6.f); }
-__device__ __forceinline__ float hsig_d(float x) { return x > -3.f && x < 3.f ? 1.f / 6.f : 0.f; }
 
 // [B][C][HW] (the batch) -> rows [B*HW][C]
 __global__ void __launch_bounds__(256) nchw_rows(const StepIn* __restrict__ in, float* __restrict__ y, int B, int C,
@@ -347,6 +332,7 @@ struct BlkP {
 };
 
 struct Plan {
+    Fused* fused;  // batches of up to kFusedMax; the buffers below are for larger ones
     BlkP bk[NBLK];
     const float *wl, *gl, *bl, *wf1, *bf1, *wf2, *bf2;
     float *gwl, *ggl, *gbl, *gwf1, *gbf1, *gwf2, *gbf2;
@@ -368,7 +354,7 @@ size_t wgrad_part_floats(int B) {
     size_t n = r64(Sb * NCLS * F1) + r64(Sb * F1 * CLAST);
     int ci = CIN;
     for (int j = 0; j < NBLK; ++j) {
-        const Blk& b = kBlk[j];
+        const Shape& b = kBlk[j];
         n += r64(S * b.co * b.e) + r64(S * b.e * ci);
         if (b.se) n += 2 * r64(Sb * b.e * se_width(b.e));
         ci = b.co;
@@ -381,7 +367,7 @@ size_t ws_floats(int B) {
     size_t s = 0;
     auto add = [&](size_t n) { s += (4 * n + 255) / 256 * 64; };  // floats, 256-byte rounded
     for (int j = 0; j < NBLK; ++j) {
-        const Blk& b = kBlk[j];
+        const Shape& b = kBlk[j];
         add(R * b.e * 2);          // xh1, a1 (input side, at most R rows)
         add(R * b.e * 3);          // xh2, a2, a2s
         add((size_t)B * b.e * 3);  // m, t (+ q)
@@ -400,7 +386,10 @@ size_t ws_floats(int B) {
     return s;
 }
 
-size_t ws_bytes(const fo_model* m) { return sizeof(Plan) + 256 + 4 * ws_floats(m->max_batch) + 256 * 256; }
+size_t ws_bytes(const fo_model* m) {
+    const size_t large = m->max_batch > kFusedMax ? 4 * ws_floats(m->max_batch) + 256 * 256 : 0;
+    return sizeof(Plan) + 256 + fused_bytes(m->max_batch) + large;
+}
 
 fo_status init(fo_model* m) {
     Plan* P = new (std::nothrow) Plan();
@@ -418,9 +407,11 @@ fo_status init(fo_model* m) {
     };
     Arena& ar = m->arena;
     ar.take<char>(sizeof(Plan));
+    const fo_status st = fused_init(m, B, &P->fused);
+    if (st != FO_OK || B <= kFusedMax) return st;
     int ci = CIN, H = HIN;
     for (int j = 0; j < NBLK; ++j) {
-        const Blk& b = kBlk[j];
+        const Shape& b = kBlk[j];
         BlkP& K = P->bk[j];
         K.H = H;
         K.Ho = (H + 2 * (b.k / 2) - b.k) / b.stride + 1;
@@ -518,6 +509,7 @@ fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
     Plan* P = (Plan*)m->plan;
     hipStream_t s = m->stream;
     const int B = acts->batch;
+    if (B <= kFusedMax) return fused_step(m, P->fused, B);
     fo_status st = FO_OK;
     auto gemm = [&](const GemmF32& g) { return launch_gemm_f32(g, P->part, P->part_floats, s); };
     // y[r][n] = x[r][:] . W[n][:] (+ bias, ReLU) for W [N][K]
@@ -580,7 +572,7 @@ fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
     const float* x = P->x0;
     int ci = CIN;
     for (int j = 0; j < NBLK; ++j) {
-        const Blk& b = kBlk[j];
+        const Shape& b = kBlk[j];
         BlkP& K = P->bk[j];
         const int Ri = B * K.H * K.H, Ro = B * K.Ho * K.Ho, HWo = K.Ho * K.Ho;
         TRY(linear(x, K.wex, nullptr, P->z, Ri, b.e, ci, 0));
@@ -637,7 +629,7 @@ fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
     float *t1 = P->d1, *t2 = P->d2;  // scratch
     TRY(linear_dx(t2, P->wl, dy, Rl, CLAST, ci, nullptr, nullptr));
     for (int j = NBLK - 1; j >= 0; --j) {
-        const Blk& b = kBlk[j];
+        const Shape& b = kBlk[j];
         BlkP& K = P->bk[j];
         const int Ri = B * K.H * K.H, Ro = B * K.Ho * K.Ho, HWo = K.Ho * K.Ho;
         const int cin = j ? kBlk[j - 1].co : CIN;
@@ -685,23 +677,15 @@ fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
 }
 
 void destroy(fo_model* m) {
-    delete (Plan*)m->plan;
+    Plan* P = (Plan*)m->plan;
+    if (P) fused_destroy(P->fused);
+    delete P;
     m->plan = nullptr;
 }
 
 }  // namespace
 
-int64_t mbv3_param_count() {
-    int64_t n = 0;
-    int ci = CIN;
-    for (const Blk& b : kBlk) {
-        n += (int64_t)b.e * ci + 2 * b.e + (int64_t)b.e * b.k * b.k + 2 * b.e;
-        if (b.se) n += 2LL * se_width(b.e) * b.e + se_width(b.e) + b.e;
-        n += (int64_t)b.co * b.e + 2 * b.co;
-        ci = b.co;
-    }
-    return n + (int64_t)CLAST * ci + 2 * CLAST + (int64_t)F1 * CLAST + F1 + (int64_t)NCLS * F1 + NCLS;
-}
+int64_t mbv3_param_count() { return mbv3::kOffs.total; }
 
 const Family* family_mbv3() {
     static const Family f = {(int64_t)CIN * HIN * HIN * 4, ws_bytes, init, step, destroy};
