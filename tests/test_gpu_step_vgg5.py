@@ -74,3 +74,21 @@ def test_three_steps_in_a_row():
             prev = out["params"]
     finally:
         A.fo_model_destroy(model)
+
+
+# Batches around the edges of the fused step (one sample, 16 and 17 padded
+# samples, more samples than shares of the weight gradient, its largest batch)
+# and one beyond it.  Bounds as above; seeds in which no ReLU input or pool
+# margin is within 9e-6 of the other branch.
+@pytest.mark.parametrize("B,sub", [(1, 60), (16, 60), (17, 61), (33, 61), (128, 63), (130, 63)])
+def test_batch_edges(B, sub):
+    torch = torch_cuda()
+    announce(f"config 9 step B={B}")
+    theta = S.init_params(CID)
+    acts = S.make_acts(CID, 1, batch=B, sub=sub)[0]
+    labels = S.make_labels(CID, 1, batch=B, sub=sub)[0]
+    model = A.fo_model_create(CID, max(B, 40), theta, torch.cuda.current_stream())
+    try:
+        _check(_step(model, to_dev(acts), to_dev(labels), B), theta.astype(np.float64), acts, labels)
+    finally:
+        A.fo_model_destroy(model)
