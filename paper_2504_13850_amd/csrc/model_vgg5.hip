@@ -145,7 +145,7 @@ constexpr int XP = 10, XS = XP * XP;  // an image with its border of zeros
 constexpr int kWgShares = 32;         // samples' shares of the convolution's weight gradient
 // offsets in the flat parameter vector
 constexpr int64_t oWc = 0, oG = oWc + (int64_t)CO * KC, oBb = oG + CO, oW1 = oBb + CO, oB1 = oW1 + (int64_t)F1 * NF,
-                  oW2 = oB1 + F1, oB2 = oW2 + (int64_t)NCLS * F1;
+                  oW2 = oB1 + F1;
 
 // One image of the batch into xs[ci][10][10] (LDS; the border is zeroed by the caller once).
 __device__ __forceinline__ void stage_image(const StepIn* in, int b, float* xs) {
@@ -172,24 +172,30 @@ __global__ void __launch_bounds__(256) v5_conv(const StepIn* __restrict__ in, co
     __shared__ float xs[CI * XS];
     const int b = blockIdx.x, lane = threadIdx.x & 63, tok = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
     const int co = blockIdx.y * 16;
+    // the weights of a tap are loaded during the products of the one before
+    const float* wr = w + (int64_t)(co + tok) * KC + 4 * g;
+    f32x4 a[2][CI / 16];
+#pragma unroll
+    for (int s = 0; s < CI / 16; ++s) a[0][s] = ld4(wr + 16 * s);
     zero_image(xs);
     stage_image(in, b, xs);
     __syncthreads();
     const int px = 16 * wave + tok, at = px / HW * XP + px % HW;
-    const float* wr = w + (int64_t)(co + tok) * KC + 4 * g;
     f32x4 acc[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+    for (int t = 0; t < 9; ++t) {
+        if (t + 1 < 9)
 #pragma unroll
-        for (int s = 0; s < CI / 16; ++s) {
-            const f32x4 a = ld4(wr + t * CI + 16 * s);
+            for (int s = 0; s < CI / 16; ++s) a[(t + 1) & 1][s] = ld4(wr + (t + 1) * CI + 16 * s);
+#pragma unroll
+        for (int s = 0; s < CI / 16; ++s)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                    a[j], xs[(16 * s + 4 * g + j) * XS + at + t / 3 * XP + t % 3], acc[j], 0, 0, 0);
-        }
+                    a[t & 1][s][j], xs[(16 * s + 4 * g + j) * XS + at + t / 3 * XP + t % 3], acc[j], 0, 0, 0);
+    }
     const f32x4 v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) z[(co + 4 * g + i) * ld + b * HW * HW + px] = v[i];
@@ -249,89 +255,6 @@ __global__ void __launch_bounds__(512) v5_bn_pool(const float* __restrict__ z, i
         const int64_t e = (int64_t)(c * HP * HP + o) * ldb + b;
         p[e] = best;
         arg[e] = (uint8_t)at;
-    }
-}
-
-// Between the hidden layer and its gradient, one workgroup: logits, mean
-// cross-entropy (labels clamped and counted), dz, df1 = dz W2 where f1 > 0, the
-// classifier's gradients and update.
-__global__ void __launch_bounds__(1024) v5_head(const float* __restrict__ f1, int ldb, const StepIn* __restrict__ in,
-                                                float* __restrict__ prm, float* __restrict__ grd, float lr, int B,
-                                                float* __restrict__ logits, float* __restrict__ loss,
-                                                float* __restrict__ df1) {
-    __shared__ float f[F1][kFusedMax + 1], dz[NCLS][kFusedMax + 1], w2[NCLS * F1], part[2];
-    __shared__ int badw[2];
-    const int t = threadIdx.x;
-    for (int e = t; e < F1 * ldb; e += 1024) f[e / ldb][e % ldb] = f1[e];
-    for (int e = t; e < NCLS * F1; e += 1024) w2[e] = prm[oW2 + e];
-    __syncthreads();
-    for (int e = t; e < B * NCLS; e += 1024) {
-        const int n = e / B, b = e % B;
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < F1; k += 4)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] = fmaf(f[k + j][b], w2[n * F1 + k + j], s[j]);
-        const float v = ((s[0] + s[1]) + (s[2] + s[3])) + prm[oB2 + n];
-        dz[n][b] = v;
-        logits[b * NCLS + n] = v;
-    }
-    __syncthreads();
-    if (t < kFusedMax) {  // a thread per sample, two waves
-        float mine = 0.f;
-        int bad = 0;
-        if (t < B) {
-            float m = -INFINITY, s = 0.f;
-#pragma unroll
-            for (int n = 0; n < NCLS; ++n) m = fmaxf(m, dz[n][t]);
-#pragma unroll
-            for (int n = 0; n < NCLS; ++n) s += expf(dz[n][t] - m);
-            const float lse = m + logf(s);
-            int y = in->labels[t];
-            if (y < 0 || y >= NCLS) {
-                bad = 1;
-                y = y < 0 ? 0 : NCLS - 1;
-            }
-            mine = lse - dz[y][t];
-#pragma unroll
-            for (int n = 0; n < NCLS; ++n) dz[n][t] = (expf(dz[n][t] - lse) - (n == y ? 1.f : 0.f)) / (float)B;
-        } else if (t < ldb) {
-#pragma unroll
-            for (int n = 0; n < NCLS; ++n) dz[n][t] = 0.f;
-        }
-        mine = wave_sum(mine);
-        for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o);
-        if ((t & 63) == 0) {
-            part[t >> 6] = mine;
-            badw[t >> 6] = bad;
-        }
-    }
-    __syncthreads();
-    if (t == 0) {
-        loss[0] = (part[0] + part[1]) / (float)B;
-        loss[1] = (float)(badw[0] + badw[1]);
-    }
-    for (int e = t; e < F1 * ldb; e += 1024) {
-        const int k = e / ldb, b = e % ldb;
-        float s = 0.f;
-#pragma unroll
-        for (int n = 0; n < NCLS; ++n) s = fmaf(dz[n][b], w2[n * F1 + k], s);
-        df1[e] = f[k][b] > 0.f ? s : 0.f;  // (padding samples: dz = 0)
-    }
-    for (int e = t; e < NCLS * F1 + NCLS; e += 1024) {
-        float s = 0.f, u = 0.f;
-        const int n = e < NCLS * F1 ? e / F1 : e - NCLS * F1;
-        if (e < NCLS * F1)
-            for (int b = 0; b < ldb; b += 2) {
-                s = fmaf(dz[n][b], f[e % F1][b], s);
-                u = fmaf(dz[n][b + 1], f[e % F1][b + 1], u);
-            }
-        else
-            for (int b = 0; b < ldb; ++b) s += dz[n][b];
-        s += u;
-        const int64_t i = oW2 + e;  // (the bias follows the weights)
-        const float old = prm[i];
-        grd[i] = s;
-        prm[i] = __builtin_fmaf(-lr, s, old);
     }
 }
 
@@ -602,8 +525,8 @@ fo_status fused_step(fo_model* m, const Plan* P, int B) {
     l.ldb = ldb;
     hipLaunchKernelGGL((linear_small<false, E_RELU>), dim3(F1 / 16, (unsigned)cdiv(ldb, 32)), dim3(LIN_T), 0, s, l);
     // loss and backward (Alg. 4: backward pass of M_s)
-    hipLaunchKernelGGL(v5_head, dim3(1), dim3(1024), 0, s, P->f1f, ldb, m->dev_in, prm, grd, m->lr, B, m->logits,
-                       m->loss, P->df1f);
+    hipLaunchKernelGGL((small_head<F1, true>), dim3(1), dim3(1024), 0, s, P->f1f, ldb, m->dev_in, prm + oW2, grd + oW2,
+                       m->lr, B, m->logits, m->loss, P->df1f);
     hipLaunchKernelGGL(v5_dp_bn, dim3(CO), dim3(512), 0, s, P->df1f, ldb, prm + oW1, P->xhc, ld, P->rsc, P->argf, prm,
                        grd, m->lr, P->dzc, B);
     const WUnit fc1{P->df1f, Act2{P->pf, 16, ldb}, oW1, oB1, F1, NF, ldb, 0};

@@ -134,6 +134,105 @@ __global__ void __launch_bounds__(LIN_T) linear_small(const Lin p) {
     }
 }
 
+// ------------------------------------------------------------------ classifier of ten classes
+// Between the last hidden layer f [F][ldb] and its gradient, one workgroup:
+// logits [B][10], mean cross-entropy (labels clamped and counted), dz, df = dz W
+// (where f > 0 if RELU), the classifier's gradients and update (prm / grd: its
+// weights [10][F], then its biases).  128 samples at a time in LDS.
+template <int F, bool RELU>
+__global__ void __launch_bounds__(1024) small_head(const float* __restrict__ f1, int ldb,
+                                                   const StepIn* __restrict__ in, float* __restrict__ prm,
+                                                   float* __restrict__ grd, float lr, int B,
+                                                   float* __restrict__ logits, float* __restrict__ loss,
+                                                   float* __restrict__ df1) {
+    constexpr int C = 10, NB = 128, NG = (C * F + C + 1023) / 1024;
+    __shared__ float f[F][NB + 1], dz[C][NB + 1], w[C * F], part[2];
+    __shared__ int badw[2];
+    const int t = threadIdx.x;
+    for (int e = t; e < C * F; e += 1024) w[e] = prm[e];
+    float grad[NG] = {}, mine = 0.f;
+    int bad = 0;
+    for (int b0 = 0; b0 < ldb; b0 += NB) {
+        const int nb = min(NB, ldb - b0), nv = min(NB, B - b0);  // samples with padding, samples
+        __syncthreads();
+        for (int e = t; e < F * nb; e += 1024) f[e / nb][e % nb] = f1[(int64_t)(e / nb) * ldb + b0 + e % nb];
+        __syncthreads();
+        for (int e = t; e < nv * C; e += 1024) {
+            const int n = e / nv, b = e % nv;
+            float s[4] = {0.f, 0.f, 0.f, 0.f};
+            for (int k = 0; k < F; k += 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s[j] = fmaf(f[k + j][b], w[n * F + k + j], s[j]);
+            const float v = ((s[0] + s[1]) + (s[2] + s[3])) + prm[C * F + n];
+            dz[n][b] = v;
+            logits[(int64_t)(b0 + b) * C + n] = v;
+        }
+        __syncthreads();
+        if (t < nv) {  // a thread per sample
+            float m = -INFINITY, s = 0.f;
+#pragma unroll
+            for (int n = 0; n < C; ++n) m = fmaxf(m, dz[n][t]);
+#pragma unroll
+            for (int n = 0; n < C; ++n) s += expf(dz[n][t] - m);
+            const float lse = m + logf(s);
+            int y = in->labels[b0 + t];
+            if (y < 0 || y >= C) {
+                ++bad;
+                y = y < 0 ? 0 : C - 1;
+            }
+            mine += lse - dz[y][t];
+#pragma unroll
+            for (int n = 0; n < C; ++n) dz[n][t] = (expf(dz[n][t] - lse) - (n == y ? 1.f : 0.f)) / (float)B;
+        } else if (t < nb) {
+#pragma unroll
+            for (int n = 0; n < C; ++n) dz[n][t] = 0.f;
+        }
+        __syncthreads();
+        for (int e = t; e < F * nb; e += 1024) {
+            const int k = e / nb, b = e % nb;
+            float s = 0.f;
+#pragma unroll
+            for (int n = 0; n < C; ++n) s = fmaf(dz[n][b], w[n * F + k], s);
+            df1[(int64_t)k * ldb + b0 + b] = !RELU || f[k][b] > 0.f ? s : 0.f;  // (padding samples: dz = 0)
+        }
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int e = t + 1024 * i;
+            float s = 0.f, u = 0.f;
+            if (e < C * F) {
+                for (int b = 0; b < nv; b += 2) {  // (an odd last sample is followed by padding or dz = 0)
+                    s = fmaf(dz[e / F][b], f[e % F][b], s);
+                    u = fmaf(b + 1 < nv ? dz[e / F][b + 1] : 0.f, f[e % F][b + 1], u);
+                }
+            } else if (e < C * F + C) {
+                for (int b = 0; b < nv; ++b) s += dz[e - C * F][b];
+            }
+            grad[i] += s + u;
+        }
+    }
+    if (t < NB) {
+        mine = wave_sum(mine);
+        for (int o = 32; o > 0; o >>= 1) bad += __shfl_xor(bad, o);
+        if ((t & 63) == 0) {
+            part[t >> 6] = mine;
+            badw[t >> 6] = bad;
+        }
+    }
+    __syncthreads();  // (also: every read of the biases is done)
+    if (t == 0) {
+        loss[0] = (part[0] + part[1]) / (float)B;
+        loss[1] = (float)(badw[0] + badw[1]);
+    }
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        const int e = t + 1024 * i;
+        if (e >= C * F + C) break;
+        const float old = prm[e];
+        grd[e] = grad[i];
+        prm[e] = __builtin_fmaf(-lr, grad[i], old);
+    }
+}
+
 // ------------------------------------------------------------------ weight gradients and their update
 // dW[n][k] = sum_r dY[n][r] X[k][r] of a product, 32 x 32 per wave (four
 // MFMA tiles fed by four 16-byte loads per 16 rows, both operands contiguous in

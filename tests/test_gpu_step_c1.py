@@ -116,3 +116,23 @@ def test_checkpoint_write_read_roundtrip():
             A.fo_model_read(model, A.FO_BUF_LOSS)  # no step yet
     finally:
         A.fo_model_destroy(model)
+
+
+# Batches whose samples are padded (17), share images in the weight gradients
+# (70 over 64 shares) and pass the classifier in two parts (130).  Bounds and
+# choice of seed as above.
+@pytest.mark.parametrize("B", [17, 70, 130])
+def test_batch_edges(B):
+    torch = torch_cuda()
+    announce(f"config 1 step B={B}")
+    theta = S.init_params(CID)
+    sub = next(k for k in range(B, B + 50)
+               if _pool_margin(CID, theta, S.make_acts(CID, 1, batch=B, sub=k)[0]) > 1e-6)
+    acts = S.make_acts(CID, 1, batch=B, sub=sub)[0]
+    labels = S.make_labels(CID, 1, batch=B, sub=sub)[0]
+    model = A.fo_model_create(CID, B, theta, torch.cuda.current_stream())
+    try:
+        A.fo_server_step(model, (to_dev(acts), None, B), to_dev(labels), 0)
+        _check_step(model, theta, acts, labels, B)
+    finally:
+        A.fo_model_destroy(model)
