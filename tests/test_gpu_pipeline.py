@@ -76,7 +76,12 @@ def _run(torch, K, B, n_slots, periods, seconds, p_drop, policy, D, sub, seed, b
 def test_concurrent_run_is_a_valid_sequential_interleaving(policy):
     torch = torch_cuda()
     K, B, n_slots, D = 8, 8, 20, 3
-    periods = 1e-3 * np.exp(np.random.default_rng(5).normal(0.0, 0.5, K))
+    # The run has to reach the pool's cap (not_sent > 0 below): together the devices
+    # send K x 0.7 present / (1.5 mean slow-down x period) = 37 batches per ms at a
+    # period of 0.1 ms, twice what the server can train (a step of 8 samples is
+    # at least 50 us on an MI355X, so at most 20 per ms).  At 1 ms they sent 4.7 per
+    # ms, within 3% of what the server trained when a step took 150 us.
+    periods = 1e-4 * np.exp(np.random.default_rng(5).normal(0.0, 0.5, K))
     announce(f"pipeline policy={policy} K={K} B={B} 0.8 s, p=0.3")
     r = _run(torch, K, B, n_slots, periods, 0.8, 0.3, policy, D, sub=41, seed=9)
     st, log = r["st"], r["log"]
