@@ -147,6 +147,28 @@ struct SplitJobs {
 };
 fo_status launch_splitk_sum_multi(const SplitJobs& jobs, hipStream_t s);
 
+// Weight gradients of several convolutions in one launch: job i forms
+// dW[co][(ky, kx, ci)] = sum over output pixels of dz[pixel][co] x[pixel at tap][ci]
+// in S_i = ceil(pixels / (32 steps)) K slices, slice z to ws_i + z Co (kh kw Ci) (the
+// caller adds them up, see SgdSums), or with one slice straight to C_i.  Output
+// maps whose width and size are powers of two; Co and Ci multiples of 8.
+constexpr int kConvWgradMax = 16;
+struct ConvWgrad {
+    const bf16_t* dz = nullptr;
+    const bf16_t* x = nullptr;
+    float* C = nullptr;
+    float* ws = nullptr;
+    ConvGeom g;
+};
+struct ConvWgrads {
+    ConvWgrad j[kConvWgradMax];
+    int n = 0;
+    int steps = 32;  // length of a slice in K tiles of 32 pixels
+};
+constexpr int kConvWgradK = 32;
+inline int conv_wgrad_slices(int64_t pixels, int steps) { return (int)cdiv(pixels, (int64_t)kConvWgradK * steps); }
+fo_status launch_conv_wgrads(const ConvWgrads& g, hipStream_t s);
+
 // Bytes of split-K workspace a descriptor needs (0 if splits == 1).
 inline size_t gemm_ws_bytes(int M, int N, int splits) {
     return splits > 1 ? sizeof(float) * (size_t)M * N * splits : 0;

@@ -1356,21 +1356,20 @@ struct DmaKRt {
     }
 };
 
-// One 128 x 128 tile of a weight-gradient product over its whole K, NST stages
+// One 128 x 128 tile of a weight-gradient product over k in [kbeg, K), B read by lb, NST stages
 // of KT-deep tiles in a ring (the copy of tile t + NST - 1 issued before the
 // MFMAs of tile t; every copy issued, past the last tile too, so that the
 // number in flight is static).  The stages (NST x 2 x KT x 128 bf16) hold the
 // fp32 C tile afterwards.
-template <int KT, int NST>
-__device__ __forceinline__ void wgrad_tile(const GemmDesc& d, const TileJob& job, int M, int K,
+template <int KT, int NST, class LB>
+__device__ __forceinline__ void wgrad_tile(const GemmDesc& d, const TileJob& job, int M, int kbeg, int K, const LB& lb,
                                            bf16_t (*smem)[2][KT * BM]) {
     static_assert(NST * 2 * KT * BM * 2 >= BM * BN * 4, "the C tile lives in the stages");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int nk = (K + KT - 1) / KT;
-    DmaKRt<KT> la, lb;
+    const int nk = K > kbeg ? (K - kbeg + KT - 1) / KT : 0;
+    DmaKRt<KT> la;
     la.init(d.lda, job.m0, M, lane, wave);
-    lb.init(d.ldb, job.n0, d.N, lane, wave);
 
     f32x16 acc[2][2];
 #pragma unroll
@@ -1382,7 +1381,7 @@ __device__ __forceinline__ void wgrad_tile(const GemmDesc& d, const TileJob& job
 
     constexpr int CPT = 2 * DmaKRt<KT>::NI;  // copy instructions per tile and thread
     auto copy_tile = [&](int st, int t) {
-        const int kb = t * KT, ke = t < nk ? K : 0;
+        const int kb = kbeg + t * KT, ke = t < nk ? K : 0;
         la.copy(d.A, kb, ke, smem[st][0], wave);
         lb.copy(d.B, kb, ke, smem[st][1], wave);
     };
@@ -1449,8 +1448,93 @@ template <int KT, int NST>
 __global__ void __launch_bounds__(NT, 2) gemm_wgrad_dma_kernel(const GemmGroupArg g) {
     __shared__ __attribute__((aligned(1024))) bf16_t smem[NST][2][KT * BM];
     for_group_tiles(g, [&](const GemmDesc& d, const TileJob& job, int M, int K) {
-        wgrad_tile<KT, NST>(d, job, M, K, smem);
+        DmaKRt<KT> lb;
+        lb.init(d.ldb, job.n0, d.N, threadIdx.x & 63, threadIdx.x >> 6);
+        wgrad_tile<KT, NST>(d, job, M, 0, K, lb, smem);
     });
+}
+
+// ------------------------------------------------------------------ convolution weight gradients
+// The B operand of a convolution's weight gradient in the same layout: rows =
+// (ky, kx, ci), k = output pixels.  A lane's chunk of eight channels belongs to
+// one tap, fixed for the tile; per copy it decodes its pixel (maps of
+// power-of-two size: shifts) and reads the input pixel of its tap, or the zero
+// block in the padding.
+struct ConvWgradJob {
+    const bf16_t* dz;
+    const bf16_t* x;
+    float* out;  // C, or the slices when S > 1
+    int Co, N, K, S, tile0, H, W, Ci, kw, stride, pad, lwo, lhw;
+};
+template <int KT>
+struct DmaConvX {
+    typedef DmaKRt<KT> L;
+    int64_t off;  // of (0, ky - pad, kx - pad, ci)
+    int iy0, ix0, kk0;
+    int H, W, Ci, stride, lwo, lhw;
+    bool ok;
+    __device__ void init(const ConvWgradJob& j, int r0, int lane, int wave) {
+        const int sub = lane / L::CPR, slot = lane % L::CPR;
+        kk0 = L::KPI * wave + sub;
+        const int r = r0 + 8 * (slot ^ (4 * (kk0 & 3)));
+        ok = r < j.N;
+        const int tap = r / j.Ci, ky = tap / j.kw, kx = tap - ky * j.kw;
+        iy0 = ky - j.pad;
+        ix0 = kx - j.pad;
+        H = j.H; W = j.W; Ci = j.Ci; stride = j.stride; lwo = j.lwo; lhw = j.lhw;
+        off = ((int64_t)iy0 * W + ix0) * Ci + (r - tap * Ci);
+    }
+    __device__ void copy(const bf16_t* X, int kb, int kend, bf16_t* tile, int wave) const {
+#pragma unroll
+        for (int v = 0; v < L::NI; ++v) {
+            const int pix = kb + kk0 + 4 * L::KPI * v;
+            const int b = pix >> lhw, y = ((pix >> lwo) & ((1 << (lhw - lwo)) - 1)) * stride,
+                      x = (pix & ((1 << lwo) - 1)) * stride;
+            const bool in = ok && pix < kend && (unsigned)(y + iy0) < (unsigned)H && (unsigned)(x + ix0) < (unsigned)W;
+            __builtin_amdgcn_global_load_lds(in ? X + (((int64_t)b * H + y) * W + x) * Ci + off : kZero8,
+                                             FO_LDS(tile + (wave + 4 * v) * 512), 16, 0, 0);
+        }
+    }
+};
+
+// Weight gradients of several convolutions, one 128 x 128 tile of one K slice per
+// workgroup, concatenated (longest K first) and renumbered so that each XCD owns
+// a contiguous range (tiles of a slice share its pixels).  One by one, register-
+// staged, they took 17.6 us each with a 7 us reduction of their slices after it
+// (VGG-16 at batch 64: 11 of them); a launch per layer leaves its last round of
+// workgroups and its reduction exposed.
+struct ConvWgradArg {
+    ConvWgradJob j[kConvWgradMax];
+    int n, tiles, slice;  // slice: pixels of a K slice
+};
+template <int KT, int NST>
+__global__ void __launch_bounds__(NT, 2) conv_wgrad_group_kernel(const ConvWgradArg g) {
+    __shared__ __attribute__((aligned(1024))) bf16_t smem[NST][2][KT * BM];
+    const int xq = g.tiles >> 3, xr = g.tiles & 7, xc = blockIdx.x & 7;
+    const int nid = xc * xq + min(xc, xr) + (blockIdx.x >> 3);
+    int ji = 0;
+    while (ji + 1 < g.n && g.j[ji + 1].tile0 <= nid) ++ji;
+    const ConvWgradJob& j = g.j[ji];
+    const int nN = (j.N + BN - 1) / BN, nM = (j.Co + BM - 1) / BM, t = nid - j.tile0, t1 = t % (nM * nN);
+    TileJob job;
+    job.zt = t / (nM * nN);
+    job.mt = t1 % nM;
+    job.m0 = job.mt * BM;
+    job.n0 = t1 / nM * BN;
+    job.S = j.S;
+    GemmDesc d;
+    d.M = j.Co;
+    d.N = j.N;
+    d.A = j.dz;
+    d.lda = j.Co;
+    d.B = j.x;
+    d.Cf = d.ws = j.out;
+    d.ldcf = j.N;
+    d.vec_epi = 1;
+    DmaConvX<KT> lb;
+    lb.init(j, job.n0, threadIdx.x & 63, threadIdx.x >> 6);
+    const int kbeg = job.zt * g.slice;
+    wgrad_tile<KT, NST>(d, job, j.Co, kbeg, min(j.K, kbeg + g.slice), lb, smem);
 }
 
 // Tall tiles: 256 x 128 per workgroup, 128 x 64 per wave (4 x 2 accumulators),
@@ -1913,6 +1997,44 @@ fo_status gemm_group(const GemmDesc* ds, int n, hipStream_t s, int max_wg) {
     else
         hipExtLaunchKernelGGL((gemm_wgrad_dma_kernel<kWgradKT, kWgradNST>), dim3(grid), dim3(NT), 0, s, ea, eb, 0,
                               g);
+    prof_end_ext(h);
+    FO_LAUNCHED();
+    return FO_OK;
+}
+
+fo_status launch_conv_wgrads(const ConvWgrads& w, hipStream_t s) {
+    FO_CHECK(w.n >= 1 && w.n <= kConvWgradMax && w.steps >= 1, "conv weight gradients: %d products", w.n);
+    auto al16 = [](const void* p) { return p && ((uintptr_t)p & 15) == 0; };
+    auto log2of = [](int n) { return n > 0 && (n & (n - 1)) == 0 ? __builtin_ctz(n) : -1; };
+    ConvWgradArg a;
+    a.n = w.n;
+    a.tiles = 0;
+    a.slice = kConvWgradK * w.steps;
+    ProfInfo pi;
+    pi.kind = PROF_FLOPS;
+    for (int i = 0; i < w.n; ++i) {
+        const ConvWgrad& c = w.j[i];
+        ConvWgradJob& j = a.j[i];
+        j.dz = c.dz;
+        j.x = c.x;
+        j.Co = c.g.Co;
+        j.N = c.g.kh * c.g.kw * c.g.Ci;
+        j.K = c.g.Bn * c.g.Ho * c.g.Wo;
+        j.S = conv_wgrad_slices(j.K, w.steps);
+        j.out = j.S > 1 ? c.ws : c.C;
+        j.tile0 = a.tiles;
+        j.H = c.g.H; j.W = c.g.W; j.Ci = c.g.Ci; j.kw = c.g.kw; j.stride = c.g.stride; j.pad = c.g.pad;
+        j.lwo = log2of(c.g.Wo);
+        j.lhw = log2of(c.g.Ho * c.g.Wo);
+        FO_CHECK(j.K >= 1 && j.lwo >= 0 && j.lhw >= j.lwo && j.Co % 8 == 0 && j.Ci % 8 == 0 && al16(j.dz) &&
+                     al16(j.x) && al16(j.out), "conv weight gradients: bad product %d", i);
+        a.tiles += (int)(cdiv(j.Co, BM) * cdiv(j.N, BN)) * j.S;
+        pi.flops += 2.0 * j.Co * j.N * j.K;
+    }
+    hipEvent_t ea, eb;
+    const int h = prof_begin_ext("conv_wgrad_group_kernel", pi, &ea, &eb);
+    hipExtLaunchKernelGGL((conv_wgrad_group_kernel<kConvWgradK, kWgradNST>), dim3(a.tiles), dim3(NT), 0, s, ea, eb, 0,
+                          a);
     prof_end_ext(h);
     FO_LAUNCHED();
     return FO_OK;

@@ -327,6 +327,96 @@ fo_status launch_sgd(float* p, const float* g, float* v, bf16_t* w16, bf16_t* w1
     return FO_OK;
 }
 
+// sgd_kernel's update with the gradient summed from its K slices on the way: a
+// block takes 4,096 elements of one range, a thread four groups of four, the
+// slices of all four in flight together.  Adding the slices here saves a pass
+// over the gradients and a launch per product (VGG-16: 11 reductions of 7 us and
+// a 38.6 us update).
+constexpr int kSumBlock = 4096;
+template <bool MOM, bool SHADOW>
+__global__ void __launch_bounds__(256) sgd_sums_kernel(const SgdSums t, float* __restrict__ p, float* __restrict__ g,
+                                                       float* __restrict__ v, bf16_t* __restrict__ w16,
+                                                       bf16_t* __restrict__ w16lo, float lr, float mu) {
+    int bid = blockIdx.x, ji = 0;
+    for (; ji < t.n - 1; ++ji) {
+        const int nb = (int)((t.j[ji].n + kSumBlock - 1) / kSumBlock);
+        if (bid < nb) break;
+        bid -= nb;
+    }
+    const int64_t n = t.j[ji].n, off = t.j[ji].off, n4 = n / 4;
+    const int S = t.j[ji].S;
+    const float* ws = t.j[ji].ws;
+    const f32x4* p4 = reinterpret_cast<const f32x4*>(p + off);
+    const f32x4* v4 = reinterpret_cast<const f32x4*>(v + off);
+    f32x4* g4 = reinterpret_cast<f32x4*>(g + off);
+    const int64_t b0 = (int64_t)bid * (kSumBlock / 4) + threadIdx.x;
+    int64_t at[4];
+    f32x4 d[4], a[4], m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // (past the end: a valid element, not stored)
+        at[u] = b0 + 256 * u < n4 ? b0 + 256 * u : (n4 ? n4 - 1 : 0);
+        if (n4) {
+            a[u] = __builtin_nontemporal_load(p4 + at[u]);
+            if (MOM) m[u] = __builtin_nontemporal_load(v4 + at[u]);
+        }
+    }
+    if (n4) {
+        if (S) {
+            const f32x4* w4 = reinterpret_cast<const f32x4*>(ws);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) d[u] = __builtin_nontemporal_load(w4 + at[u]);
+            for (int z = 1; z < S; ++z)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) d[u] += __builtin_nontemporal_load(w4 + z * n4 + at[u]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b0 + 256 * u < n4) __builtin_nontemporal_store(d[u], g4 + at[u]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) d[u] = g4[at[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b0 + 256 * u < n4)
+                sgd_store<MOM, SHADOW>(p + off, v + off, w16 + off, w16lo + off, at[u], a[u], d[u], m[u], lr, mu);
+    }
+    const int64_t e = n4 * 4 + threadIdx.x;  // the last range's odd end (gradients in g)
+    if (bid == 0 && e < n) {
+        float x = g[off + e];
+        if (MOM) {
+            x = __builtin_fmaf(mu, v[off + e], x);
+            v[off + e] = x;
+        }
+        const float y = __builtin_fmaf(-lr, x, p[off + e]);
+        p[off + e] = y;
+        if (SHADOW) {
+            const bf16_t h = f2bf(y);
+            w16[off + e] = h;
+            w16lo[off + e] = f2bf(y - bf2f(h));
+        }
+    }
+}
+
+fo_status launch_sgd_sums(const SgdSums& t, float* p, float* g, float* v, bf16_t* w16, bf16_t* w16lo, float lr,
+                          float mu, hipStream_t s) {
+    FO_CHECK(t.n >= 1 && t.n <= kSgdSumsMax && w16 && w16lo, "sgd sums: %d ranges", t.n);
+    int64_t blocks = 0;
+    for (int i = 0; i < t.n; ++i) {
+        const SgdSum& j = t.j[i];
+        FO_CHECK(j.n >= 1 && j.off % 4 == 0 && (j.n % 4 == 0 || (i == t.n - 1 && j.S == 0)) && (j.S == 0 || j.ws),
+                 "sgd sums: bad range %d", i);
+        blocks += cdiv(j.n, kSumBlock);
+    }
+    if (v)
+        hipLaunchKernelGGL((sgd_sums_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, s, t, p, g, v, w16,
+                           w16lo, lr, mu);
+    else
+        hipLaunchKernelGGL((sgd_sums_kernel<false, true>), dim3((unsigned)blocks), dim3(256), 0, s, t, p, g, v, w16,
+                           w16lo, lr, mu);
+    FO_LAUNCHED();
+    return FO_OK;
+}
+
 // The same plain update (no momentum) restricted to a list of parameter ranges:
 // block b updates elements [chunks[2b], chunks[2b] + chunks[2b + 1]) with the
 // arithmetic of sgd_kernel; used for the parameters whose update is not fused

@@ -40,6 +40,22 @@ fo_status launch_sgd(float* p, const float* g, float* v, bf16_t* w16, bf16_t* w1
 // array, one block per range).
 fo_status launch_sgd_chunks(float* p, const float* g, bf16_t* w16, bf16_t* w16lo, const int64_t* chunks,
                             int nchunks, float lr, hipStream_t s);
+// The update of ranges of the parameter vector whose gradients may still be K
+// slices: range i is [off_i, off_i + n_i); with S_i > 0 its gradient is the sum of
+// the S_i slices of n_i floats at ws_i (stored to g), else it is in g already.
+// Ranges are multiples of 4 long and aligned but the last, in ascending order.
+constexpr int kSgdSumsMax = 64;
+struct SgdSum {
+    const float* ws = nullptr;
+    int S = 0;
+    int64_t off = 0, n = 0;
+};
+struct SgdSums {
+    SgdSum j[kSgdSumsMax];
+    int n = 0;
+};
+fo_status launch_sgd_sums(const SgdSums& t, float* p, float* g, float* v, bf16_t* w16, bf16_t* w16lo, float lr,
+                          float mu, hipStream_t s);
 // y = bf16(x), ylo = bf16(x - y) (ylo may be NULL)
 fo_status launch_cast_bf16(const float* x, bf16_t* y, bf16_t* ylo, int64_t n, hipStream_t s);
 

@@ -10,6 +10,7 @@
 // Forward GEMMs are compensated split-bf16 products (high and low parts of the
 // activations and weights); backward GEMMs use the high parts.  The input
 // gradient of the first server layer is never formed.
+#include <algorithm>
 #include <vector>
 
 #include "gemm.h"
@@ -51,7 +52,6 @@ struct Conv {
     int cin, cout, k, stride, pad, H, W, Ho, Wo;
     int64_t w, b;               // parameter offsets (b < 0: no bias)
     int64_t g, be;              // batch-norm scale / shift offsets (< 0: none)
-    int splits;                 // K slices of the weight gradient
     int fsplits, dsplits;       // K slices of the forward and of the input gradient
     // activations
     bf16_t *yh, *yl;            // VGG: post-ReLU output (hi, lo)
@@ -59,7 +59,8 @@ struct Conv {
     float* part;                // ResNet: the norm's per-row-block partial sums
     float *dzf, *dzpart;        // VGG: fp32 gradient of the pre-activation, and the
                                 // partial rows of its column sums (the bias gradient)
-    float* wgws;                // the weight gradient's own split-K partials (splits > 1)
+    bf16_t* dzb;                // bf16 gradient of the convolution's output (the GEMMs' operand)
+    float* wgws;                // the weight gradient's K slices
 };
 
 struct Pool {
@@ -93,8 +94,9 @@ struct Plan {
     bf16_t *gaph, *gapl;
     float* dz;                // dlogits [B][classes]
     bf16_t* dzb;
+    bf16_t* fdb[2];           // VGG: gradients of the hidden layers (the GEMMs' operand)
     float *df[3];             // gradient ping-pong (fp32)
-    bf16_t *db[2];            // gradient (bf16 GEMM operand)
+    int wsteps;               // length of a K slice of the weight gradients (tiles of 32 pixels)
     float *dsc, *dtmp;        // ResNet shortcut / scratch gradients
     float *splitws, *redws;
     size_t act_max;           // elements of the largest activation
@@ -133,7 +135,6 @@ void build(Plan& P, int cid, int B) {
         // (the ResNet forward's partials go to its norm's statistics kernel,
         // which sums at most kBnMaxSplits slices)
         const int min_k = P.resnet ? 128 : 256;
-        c.splits = split_for(cout, k * k * cin, B * c.Ho * c.Wo, min_k);
         c.fsplits = split_for(B * c.Ho * c.Wo, cout, 3 * (int)cdiv(k * k * cin, 64) * 64, min_k,
                               P.resnet ? kBnMaxSplits : kMaxSplits);
         c.dsplits = split_for(B * H * H, cin, k * k * cout, min_k);
@@ -186,6 +187,21 @@ void build(Plan& P, int cid, int B) {
         f.b = o; o += f.out;
         P.fcs.push_back(f);
     }
+    // Weight gradients: slices about as long as give two rounds of two
+    // workgroups per CU over all layers together (VGG at batch 64: 33,600 tile
+    // steps, so 1,024 pixels; shorter ones write more partial sums, longer ones
+    // leave the last round unbalanced), at least 256 pixels so that a
+    // workgroup's ring fill stays small against its walk.
+    int64_t steps = 0;
+    for (const Conv& c : P.convs)
+        steps += cdiv(c.cout, 128) * cdiv(c.k * c.k * c.cin, 128) * cdiv((int64_t)B * c.Ho * c.Wo, kConvWgradK);
+    P.wsteps = 8;
+    while (P.wsteps < 64 && P.wsteps * 1024 < steps) P.wsteps *= 2;
+}
+// Floats of a convolution's weight-gradient slices (0 with one slice).
+size_t wgrad_ws(const Plan& P, const Conv& c, int B) {
+    const int S = conv_wgrad_slices((int64_t)B * c.Ho * c.Wo, P.wsteps);
+    return S > 1 ? (size_t)S * c.cout * c.k * c.k * c.cin : 0;
 }
 
 int64_t count_params(int cid) {
@@ -215,8 +231,8 @@ size_t ws_bytes(const fo_model* m) {
         amax = std::max(amax, n);
         if (P.resnet) { add(4 * n); add(4 * c.cout); add(4 * c.cout); add(4 * bn_ws_floats(B * c.Ho * c.Wo, c.cout)); }
         else { add(2 * n); add(2 * n); add(4 * n); add(4 * colsum_ws_floats(B * c.Ho * c.Wo, c.cout)); }
-        if (P.resnet) add(gemm_ws_bytes(c.cout, c.k * c.k * c.cin, c.splits));  // wgws
-        sw = std::max(sw, gemm_ws_bytes(c.cout, c.k * c.k * c.cin, c.splits));
+        add(2 * n);                   // dzb
+        add(4 * wgrad_ws(P, c, B));   // wgws
         sw = std::max(sw, gemm_ws_bytes(B * c.Ho * c.Wo, c.cout, c.fsplits));
         sw = std::max(sw, gemm_ws_bytes(B * c.H * c.W, c.cin, c.dsplits));
         red = std::max(red, bn_ws_floats(B * c.Ho * c.Wo, c.cout));
@@ -239,8 +255,8 @@ size_t ws_bytes(const fo_model* m) {
     }
     add(4 * (size_t)B * 512); add(2 * (size_t)B * 512); add(2 * (size_t)B * 512);
     add(4 * (size_t)B * 128); add(2 * (size_t)B * 128);
+    for (int i = 0; i < 2; ++i) add(2 * (size_t)B * 512);
     for (int i = 0; i < 3; ++i) add(4 * amax);
-    for (int i = 0; i < 2; ++i) add(2 * amax);
     add(4 * amax); add(4 * amax);
     add(sw + 256);
     add(4 * red + 256);
@@ -272,9 +288,9 @@ fo_status init(fo_model* m) {
             c.dzf = a.take<float>(n);
             c.dzpart = a.take<float>(colsum_ws_floats(B * c.Ho * c.Wo, c.cout));
         }
-        c.wgws = P->resnet && c.splits > 1 ? a.take<float>(gemm_ws_bytes(c.cout, c.k * c.k * c.cin, c.splits) / 4)
-                                           : nullptr;
-        sw = std::max(sw, gemm_ws_bytes(c.cout, c.k * c.k * c.cin, c.splits));
+        c.dzb = a.take<bf16_t>(n);
+        const size_t wn = wgrad_ws(*P, c, B);
+        c.wgws = wn ? a.take<float>(wn) : nullptr;
         sw = std::max(sw, gemm_ws_bytes(B * c.Ho * c.Wo, c.cout, c.fsplits));
         sw = std::max(sw, gemm_ws_bytes(B * c.H * c.W, c.cin, c.dsplits));
         red = std::max(red, bn_ws_floats(B * c.Ho * c.Wo, c.cout));
@@ -306,8 +322,8 @@ fo_status init(fo_model* m) {
     P->gapl = a.take<bf16_t>((size_t)B * 512);
     P->dz = a.take<float>((size_t)B * 128);
     P->dzb = a.take<bf16_t>((size_t)B * 128);
+    for (int i = 0; i < 2; ++i) P->fdb[i] = a.take<bf16_t>((size_t)B * 512);
     for (int i = 0; i < 3; ++i) P->df[i] = a.take<float>(amax);
-    for (int i = 0; i < 2; ++i) P->db[i] = a.take<bf16_t>(amax);
     P->dsc = a.take<float>(amax);
     P->dtmp = a.take<float>(amax);
     P->splitws = a.take<float>(sw / 4 + 64);
@@ -341,29 +357,44 @@ GemmDesc conv_fwd_desc(const fo_model* m, const Conv& c, int B, const bf16_t* xh
     return d;
 }
 
-// Weight gradient.  Nothing reads it before the update, so with `sums` its
-// split slices stay in the conv's own workspace and join the set that the step
-// adds up in one launch at the end of the backward (ResNet: 1.029 -> 0.981 ms
-// per step); without, the slices are summed right away (VGG, whose larger
-// partial sets are cheaper to sum while they are still in cache: 1.070 ms
-// against 1.080 deferred).
-fo_status conv_wgrad(fo_model* m, const Plan* P, const Conv& c, int B, const bf16_t* dzb, const bf16_t* xh,
-                     SplitJobs* sums) {
-    GemmDesc d;
-    d.M = c.cout; d.N = c.k * c.k * c.cin; d.K = B * c.Ho * c.Wo;
-    d.amode = OP_KR; d.A = dzb; d.lda = c.cout;
-    d.bmode = OP_CONV_DWX; d.B = xh;
-    d.g = geom(c, B);
-    d.Cf = m->grads + c.w; d.ldcf = d.N;
-    d.splits = c.splits;
-    d.ws = sums ? c.wgws : P->splitws;
-    if (sums && c.splits > 1) {
-        FO_CHECK(sums->n < kSplitJobsMax, "cnn16: more than %d deferred weight-gradient sums", kSplitJobsMax);
-        d.defer_reduce = true;
-        SplitJob& j = sums->j[sums->n++];
-        j.ws = c.wgws; j.C = d.Cf; j.ldc = d.ldcf; j.S = c.splits; j.M = d.M; j.N = d.N;
+// Weight gradient of dz (its dzb) and its input x: joins the set that runs as
+// one launch after the backward, as nothing reads it before the update.
+void add_wgrad(ConvWgrads& w, const Conv& c, const fo_model* m, int B, const bf16_t* x) {
+    ConvWgrad& j = w.j[w.n++];
+    j.dz = c.dzb;
+    j.x = x;
+    j.C = m->grads + c.w;
+    j.ws = c.wgws;
+    j.g = geom(c, B);
+}
+// The weight gradients (longest reductions, the first layers, first) and the
+// update of every parameter, adding up their slices.
+fo_status wgrads_and_update(fo_model* m, const Plan* P, int B, ConvWgrads& w, hipStream_t s) {
+    w.steps = P->wsteps;
+    std::reverse(w.j, w.j + w.n);
+    TRY(launch_conv_wgrads(w, s));
+    SgdSums t;
+    int64_t done = 0;
+    auto rest = [&](int64_t to) {  // gradients that are complete
+        if (to > done) {
+            SgdSum& j = t.j[t.n++];
+            j.off = done;
+            j.n = to - done;
+        }
+    };
+    for (const Conv& c : P->convs) {
+        const int S = conv_wgrad_slices((int64_t)B * c.Ho * c.Wo, P->wsteps);
+        if (S <= 1) continue;
+        rest(c.w);
+        SgdSum& j = t.j[t.n++];
+        j.ws = c.wgws;
+        j.S = S;
+        j.off = c.w;
+        j.n = (int64_t)c.cout * c.k * c.k * c.cin;
+        done = c.w + j.n;
     }
-    return gemm(d, m->stream);
+    rest(m->n_params);
+    return launch_sgd_sums(t, m->params, m->grads, m->mom, m->w16, m->w16lo, m->lr, m->momentum, s);
 }
 
 // input gradient: dx = conv^T(dz); optional ReLU mask (the input's own values),
@@ -455,48 +486,41 @@ fo_status step_vgg(fo_model* m, Plan* P, int B, const int32_t* labels) {
     ColSums bias_sums;
     const size_t fcpart = colsum_ws_floats(B, 512);
     TRY(launch_to_bf16(P->dz, P->dzb, (int64_t)B * f2.out, s));
-    TRY(fc_bwd(m, P, f2, B, P->dz, P->dzb, f1.yh, f1.yh, P->df[0], P->db[0], &bias_sums, P->redws));
-    TRY(fc_bwd(m, P, f1, B, P->df[0], P->db[0], f0.yh, f0.yh, P->df[1], P->db[1], &bias_sums, P->redws + fcpart));
+    TRY(fc_bwd(m, P, f2, B, P->dz, P->dzb, f1.yh, f1.yh, P->df[0], P->fdb[0], &bias_sums, P->redws));
+    TRY(fc_bwd(m, P, f1, B, P->df[0], P->fdb[0], f0.yh, f0.yh, P->df[1], P->fdb[1], &bias_sums, P->redws + fcpart));
     const Pool& last = P->pools.back();
-    TRY(fc_bwd(m, P, f0, B, P->df[1], P->db[1], last.yh, nullptr, P->df[2], nullptr, &bias_sums,
+    TRY(fc_bwd(m, P, f0, B, P->df[1], P->fdb[1], last.yh, nullptr, P->df[2], nullptr, &bias_sums,
                P->redws + 2 * fcpart));
-    // Backward through the convolutions.  db[0] and db[1] alternate as the bf16
-    // gradient of a conv's pre-activation (the GEMMs' operand); its fp32 copy
-    // goes to the conv's own dzf, whose column sums (the bias gradients) run
-    // for all convs in one pass at the end.  df[2] holds the gradient of a
-    // pool's output.
-    const bf16_t* gb = nullptr;
-    int pf = 0;
+    // Backward through the convolutions.  The gradient of a conv's
+    // pre-activation goes to its dzb (the GEMMs' operand; the weight gradients
+    // read them all after the backward) and, in fp32, to its dzf, whose column
+    // sums (the bias gradients) run for all convs in one pass at the end.
+    // df[2] holds the gradient of a pool's output.
+    ConvWgrads wg;
     for (int idx = (int)P->order.size() - 1; idx >= 0; --idx) {
         const int op = P->order[idx];
         if (op < 0) {
             // pool: route to the window winner, mask with the producing conv's ReLU
             const Pool& p = P->pools[-op - 1];
             const Conv& prod = P->convs[P->order[idx - 1]];
-            TRY(launch_maxpool_relu_bwd(P->df[2], p.arg, prod.yh, prod.dzf, P->db[pf], B, p.H, p.W, p.C, s));
-            gb = P->db[pf];
-            pf ^= 1;
+            TRY(launch_maxpool_relu_bwd(P->df[2], p.arg, prod.yh, prod.dzf, prod.dzb, B, p.H, p.W, p.C, s));
             continue;
         }
         const Conv& c = P->convs[op];
         bias_sums.add(c.dzf, c.cout, B * c.Ho * c.Wo, c.cout, c.dzpart, m->grads + c.b);
         const int prev = idx > 0 ? P->order[idx - 1] : 0;
-        const bf16_t* in = idx == 0 ? P->xin : (prev >= 0 ? P->convs[prev].yh : P->pools[-prev - 1].yh);
-        TRY(conv_wgrad(m, P, c, B, gb, in, nullptr));
+        add_wgrad(wg, c, m, B, idx == 0 ? P->xin : (prev >= 0 ? P->convs[prev].yh : P->pools[-prev - 1].yh));
         if (idx == 0) break;  // the first server layer: no input gradient
         if (prev >= 0) {
             // the input is a conv's ReLU output: mask in the epilogue
             const Conv& pc = P->convs[prev];
-            TRY(conv_dgrad(m, c, B, gb, pc.yh, nullptr, pc.dzf, P->db[pf]));
-            gb = P->db[pf];
-            pf ^= 1;
+            TRY(conv_dgrad(m, c, B, c.dzb, pc.yh, nullptr, pc.dzf, pc.dzb));
         } else {
-            TRY(conv_dgrad(m, c, B, gb, nullptr, nullptr, P->df[2], nullptr));
-            gb = nullptr;
+            TRY(conv_dgrad(m, c, B, c.dzb, nullptr, nullptr, P->df[2], nullptr));
         }
     }
     TRY(launch_colsums(bias_sums, s));
-    return launch_sgd(m->params, m->grads, nullptr, m->w16, m->w16lo, m->n_params, m->lr, 0.f, s);
+    return wgrads_and_update(m, P, B, wg, s);
 }
 
 // ------------------------------------------------------------------ ResNet
@@ -547,7 +571,7 @@ fo_status step_resnet(fo_model* m, Plan* P, int B, const int32_t* labels) {
     // gradient of the last block's output (through the average pool and its ReLU)
     float* gout = P->df[0];
     TRY(launch_gap_relu_bwd(P->df[1], lastb.outh, gout, B, hw, 512, s));
-    SplitJobs wsums;
+    ConvWgrads wg;
     for (int bi = (int)P->blocks.size() - 1; bi >= 0; --bi) {
         Block& b = P->blocks[bi];
         Conv &c1 = P->convs[b.c1], &c2 = P->convs[b.c2];
@@ -555,13 +579,13 @@ fo_status step_resnet(fo_model* m, Plan* P, int B, const int32_t* labels) {
         float* g = P->df[1];  // gradient of the pre-ReLU sum (stored by the first norm backward)
         // main branch: second conv + norm (its input gradient is gout through the block's ReLU)
         TRY(launch_bn_bwd(gout, b.outh, g, c2.z, c2.mean, c2.rstd, m->params + c2.g, rows, c2.cout, m->grads + c2.g,
-                          m->grads + c2.be, nullptr, P->db[0], c2.part, s));
-        TRY(conv_wgrad(m, P, c2, B, P->db[0], b.a1h, &wsums));
-        TRY(conv_dgrad(m, c2, B, P->db[0], b.a1h, nullptr, P->dtmp, nullptr));
+                          m->grads + c2.be, nullptr, c2.dzb, c2.part, s));
+        add_wgrad(wg, c2, m, B, b.a1h);
+        TRY(conv_dgrad(m, c2, B, c2.dzb, b.a1h, nullptr, P->dtmp, nullptr));
         TRY(launch_bn_bwd(P->dtmp, nullptr, nullptr, c1.z, c1.mean, c1.rstd, m->params + c1.g, rows, c1.cout,
-                          m->grads + c1.g, m->grads + c1.be, nullptr, P->db[1], c1.part, s));
+                          m->grads + c1.g, m->grads + c1.be, nullptr, c1.dzb, c1.part, s));
         const bf16_t* xin_h = bi == 0 ? P->xin : P->blocks[bi - 1].outh;
-        TRY(conv_wgrad(m, P, c1, B, P->db[1], xin_h, &wsums));
+        add_wgrad(wg, c1, m, B, xin_h);
         const bool need_dx = bi > 0;
         float* gnext = P->df[2];
         // shortcut branch
@@ -569,20 +593,19 @@ fo_status step_resnet(fo_model* m, Plan* P, int B, const int32_t* labels) {
         if (b.cd >= 0) {
             Conv& cd = P->convs[b.cd];
             TRY(launch_bn_bwd(g, nullptr, nullptr, cd.z, cd.mean, cd.rstd, m->params + cd.g, rows, cd.cout,
-                              m->grads + cd.g, m->grads + cd.be, nullptr, P->db[0], cd.part, s));
-            TRY(conv_wgrad(m, P, cd, B, P->db[0], xin_h, &wsums));
-            if (need_dx) TRY(conv_dgrad(m, cd, B, P->db[0], nullptr, nullptr, P->dsc, nullptr));
+                              m->grads + cd.g, m->grads + cd.be, nullptr, cd.dzb, cd.part, s));
+            add_wgrad(wg, cd, m, B, xin_h);
+            if (need_dx) TRY(conv_dgrad(m, cd, B, cd.dzb, nullptr, nullptr, P->dsc, nullptr));
             sc_grad = P->dsc;
         }
         if (need_dx) {
-            TRY(conv_dgrad(m, c1, B, P->db[1], nullptr, sc_grad, gnext, nullptr));
+            TRY(conv_dgrad(m, c1, B, c1.dzb, nullptr, sc_grad, gnext, nullptr));
             // the block input is the previous block's output: next iteration masks it
             std::swap(P->df[0], P->df[2]);
             gout = P->df[0];
         }
     }
-    if (wsums.n) TRY(launch_splitk_sum_multi(wsums, s));
-    return launch_sgd(m->params, m->grads, m->mom, m->w16, m->w16lo, m->n_params, m->lr, m->momentum, s);
+    return wgrads_and_update(m, P, B, wg, s);
 }
 
 fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {

@@ -5,7 +5,7 @@
 
 namespace fo {
 
-enum ProfKind : int { PROF_GEMM = 0, PROF_ATTN_FWD = 1, PROF_ATTN_BWD = 2, PROF_OTHER = 3 };
+enum ProfKind : int { PROF_GEMM = 0, PROF_ATTN_FWD = 1, PROF_ATTN_BWD = 2, PROF_OTHER = 3, PROF_FLOPS = 4 };
 
 struct ProfInfo {
     int kind = PROF_OTHER;
@@ -19,6 +19,8 @@ struct ProfInfo {
     // attention: cu[B+1] packed offsets, width d
     const int* cu = nullptr;
     int B = 0, d = 0;
+    // PROF_FLOPS: a matrix-core launch whose FLOPs are known at the launch
+    double flops = 0;
 };
 
 // Returns a record handle (>= 0) when the calling thread is profiling, else -1.
