@@ -70,9 +70,9 @@ struct GemmDesc {
     bf16_t* sgd_hi = nullptr;
     bf16_t* sgd_lo = nullptr;
     float sgd_lr = 0.f;
-    // Column sums of the stored value: colpart[m / 128][n] = sum of v over the
-    // valid rows of that 128-row tile (no split-K); launch_colsum_finish with
-    // rows_per_part 128 completes them.
+    // Column sums of the stored value: colpart[m / tile][n] = sum of v over the
+    // valid rows of that tile of rows (no split-K); launch_colsum_finish with
+    // rows_per_part gemm_tile(d) completes them.
     float* colpart = nullptr;
     // split-K: z-slices write fp32 partials to ws[z][M][N]; a second pass sums
     // them and runs the epilogue.
@@ -84,20 +84,25 @@ struct GemmDesc {
     const int* Mdev = nullptr;
     const int* Kdev = nullptr;
     int* prof_snap = nullptr;  // set by the launcher when profiling: receives (M, K) effective
+    int tile = 128;            // set by the launcher: edge of the output tiles (gemm_tile)
     int vec_epi = 0;           // set by the launcher: the epilogue may move four columns per access
     // With split-K: leave the partials in ws and skip the reduction pass; the
     // consumer sums them (see SplitRows).  A launch that runs unsplit (one
     // active slice) still applies its epilogue and writes Cf.
     bool defer_reduce = false;
+    // Nonzero: the sum over K is that of `splits` slices added in order, to the
+    // bit, whatever kernel runs (it may add them itself: gemm_slices_left).  For
+    // compensated forwards, whose last bits decide units at a ReLU's or pool's switch.
+    int ordered = 0;
 };
 
 // Split-K slices a launch with a device-side row bound M_eff uses: as many as
-// keep two workgroups per CU busy over the active 128 x 128 tiles, each slice
+// keep two workgroups per CU busy over the active tile x tile tiles, each slice
 // at least four 64-long K tiles (ktot: the reduction length including the
 // compensated segments).  With a static row count every launched slice is used.
-__device__ __forceinline__ int gemm_active_splits(int splits, int M_eff, int N, int ktot) {
+__device__ __forceinline__ int gemm_active_splits(int splits, int M_eff, int N, int ktot, int tile) {
     if (splits <= 1) return splits;
-    const int tiles = ((M_eff + 127) / 128) * ((N + 127) / 128);
+    const int tiles = ((M_eff + tile - 1) / tile) * ((N + tile - 1) / tile);
     int s = min(splits, max(1, 512 / max(tiles, 1)));
     while (s > 1 && ktot < 4 * 64 * s) --s;
     return s;
@@ -112,9 +117,19 @@ struct SplitRows {
     const float* ws = nullptr;    // [splits][M][N] (NULL: x only)
     const float* bias = nullptr;  // [N] or NULL
     const float* resid = nullptr; // [M][N] or NULL
-    int M = 0, N = 0, splits = 1, ktot = 0;
-    __device__ int active(int M_eff) const { return ws ? gemm_active_splits(splits, M_eff, N, ktot) : 1; }
+    int M = 0, N = 0, splits = 1, ktot = 0, tile = 128;
+    __device__ int active(int M_eff) const { return ws ? gemm_active_splits(splits, M_eff, N, ktot, tile) : 1; }
 };
+
+// Edge of the output tiles (64 or 128) that gemm() will run d on.
+int gemm_tile(const GemmDesc& d);
+// Slices that d leaves in ws to its reduction pass or consumer (1: Cf is written).
+int gemm_slices_left(const GemmDesc& d);
+
+// K slices (at most maxs) for a product of static sizes whose partials have
+// ws_floats of workspace.
+int gemm_splits(const GemmDesc& d, int maxs, int64_t ws_floats);
+constexpr int64_t kSplitFloats = (int64_t)512 * 64 * 64;  // enough for what gemm_splits gives 64 x 64 tiles
 
 // Enqueues the GEMM (and its split-K reduction) on stream s.
 fo_status gemm(const GemmDesc& d, hipStream_t s);

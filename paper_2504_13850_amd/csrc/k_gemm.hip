@@ -20,6 +20,7 @@
 //    256 x 128 tiles (128 x 64 per wave) for groups that share the GPU.
 //  - gemm_rk_krt_dma_kernel: row-major A times k-major B (input gradients),
 //    the same copies and ring.
+// Small products (gemm_tile) run on 64 x 64 tiles instead: gemm_ks_kernel.
 #include <algorithm>
 #include <type_traits>
 
@@ -621,12 +622,13 @@ struct EpiIn4 {  // as EpiIn, four columns (bf16 operands as raw bits)
     u32x2 mask = {0x3F803F80u, 0x3F803F80u}, dact = {0x3F803F80u, 0x3F803F80u};  // 1.0 x 4
 };
 
+template <bool SGD = true>
 __device__ __forceinline__ EpiIn4 epi_load4(const GemmDesc& d, int row, int col) {
     EpiIn4 e;
     if (d.resid) e.resid = *reinterpret_cast<const f32x4*>(d.resid + (int64_t)row * d.ldr + col);
     if (d.mask) e.mask = *reinterpret_cast<const u32x2*>(d.mask + (int64_t)row * d.ldm + col);
     if (d.dact) e.dact = *reinterpret_cast<const u32x2*>(d.dact + (int64_t)row * d.ldm + col);
-    if (d.sgd_theta) e.theta = *reinterpret_cast<const f32x4*>(d.sgd_theta + (int64_t)row * d.ldcf + col);
+    if (SGD && d.sgd_theta) e.theta = *reinterpret_cast<const f32x4*>(d.sgd_theta + (int64_t)row * d.ldcf + col);
     return e;
 }
 
@@ -674,6 +676,7 @@ __device__ __forceinline__ void epi_load_batch(const GemmDesc& d, const int (&ro
 }
 
 // v already holds bias and residual
+template <bool SGD = true>
 __device__ __forceinline__ f32x4 epi_store4(const GemmDesc& d, int row, int col, f32x4 v, const EpiIn4& e) {
     if (d.act == ACT_GELU) {
         if (d.dact_out) {
@@ -701,7 +704,7 @@ __device__ __forceinline__ f32x4 epi_store4(const GemmDesc& d, int row, int col,
     }
     if (d.dact) v *= bf4_to_f(e.dact);
     if (d.Cf) *reinterpret_cast<f32x4*>(d.Cf + (int64_t)row * d.ldcf + col) = v;
-    if (d.sgd_theta) {
+    if (SGD && d.sgd_theta) {
         const int64_t o = (int64_t)row * d.ldcf + col;
         f32x4 th = e.theta, lo;
 #pragma unroll
@@ -732,7 +735,7 @@ __device__ __forceinline__ int gemm_kseg(const GemmDesc& d, int Keff) {
 // two workgroups per CU busy over the active tiles, each at least four K tiles
 // long.  With static sizes every launched slice is used.
 __device__ __forceinline__ int active_splits(const GemmDesc& d, int M_eff, int ktot) {
-    return d.Mdev ? gemm_active_splits(d.splits, M_eff, d.N, ktot) : d.splits;
+    return d.Mdev ? gemm_active_splits(d.splits, M_eff, d.N, ktot, d.tile) : d.splits;
 }
 
 // The output tile and K slice of a workgroup.
@@ -784,7 +787,7 @@ __device__ __forceinline__ void drain_tile(const GemmDesc& d, float* Cs, const T
     // TPR threads per row in the four-column path, RP rows per pass; HP row
     // groups in the one-column path
     constexpr int TPR = BNt / 4, RP = NTt / TPR, HP = NTt / BNt;
-    static_assert(HP >= 1, "tile shape");
+    static_assert(HP >= 1 && BMt % (NB * RP) == 0 && BMt % (NB * HP) == 0, "a batch of rows stays in the tile");
     if (d.vec_epi) {
         // four columns per thread: rows tid / TPR + RP u, columns n0 + 4 (tid % TPR) .. + 3
         const int m0 = job.m0, c4 = (tid % TPR) * 4, col = job.n0 + c4, rr = tid / TPR;
@@ -1788,6 +1791,399 @@ __global__ void __launch_bounds__(NT, 2) gemm_rk_krt_dma_kernel(const GemmDesc d
     store_tile(d, acc, reinterpret_cast<float*>(&smem[0][0][0]), job, M, tid);
 }
 
+// ------------------------------------------------------------------ small products: K dealt to the waves
+// Products with too few 128 x 128 tiles for the chip.  In those kernels a few
+// workgroups walk a long K, each step as long as its copy's latency, or many
+// slices write and reread partial sums.  Here: 64 x 64 tiles whose K tiles are
+// dealt to the NW waves of a workgroup in turn.  Each wave holds a whole 64 x 64
+// accumulator and copies its own operands into its own 16 KB of LDS
+// (global_load_lds), so the loop has no barrier: wait for the copy, take the
+// fragments into registers, start the next copy over them, multiply.  Two
+// workgroups of four waves per CU, or one of eight, cover each other's waits.  The
+// accumulators are added in LDS before the epilogue.
+// KT k per step: 32 with the low parts (four operand tiles), 64 without.
+// Bound by operand bytes: a step moves 16 KB per wave for 24 (16) MFMAs, and with
+// all CUs busy the copies reach 13-15 TB/s out of the L2s (90% hits); 128-byte
+// rows (64 k of the low parts too) moved no faster.  VGG-16 at batch 64, conv
+// 256 -> 256 on 8 x 8 maps: forward 25.7 us whole, against about 21 and a 7 us sum
+// of its slices; input gradient 14 against 18 + 7.
+constexpr int SB = 64;
+constexpr int kKsStage = 8192;  // bf16 elements of a wave's stage
+
+// One 16-byte chunk per lane from p into LDS.  The address is opaque to the
+// compiler, which would otherwise turn a lane's choice between the operand and
+// kZero8 into two masked copies.
+__device__ __forceinline__ void ks_copy16(const bf16_t* p, bf16_t* lds) {
+    uint64_t a = (uint64_t)p;
+    asm volatile("" : "+v"(a));
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)a, FO_LDS(lds), 16, 0, 0);
+}
+
+// Row-major operand (k contiguous), 64 rows x 32 k per block in DmaRKc's layout.
+struct KsRK {
+    int64_t off[4];
+    int koff;
+    __device__ void init(const GemmDesc& d, bool is_a, int r0, int R, int kb, int lane) {
+        const int64_t ld = is_a ? d.lda : d.ldb;
+        koff = 8 * ((lane & 3) ^ ((lane >> 4) & 3));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int gr = r0 + 16 * v + (lane >> 2);
+            off[v] = gr < R ? (int64_t)gr * ld : -1;
+        }
+    }
+    // NB blocks of 32 k from kb on, block a at tile + a SB 32
+    template <int NB>
+    __device__ void copy(const bf16_t* P, int kb, int kend, bf16_t* tile) const {
+#pragma unroll
+        for (int a = 0; a < NB; ++a) {
+            const int k = kb + 32 * a + koff;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                ks_copy16(off[v] >= 0 && k < kend ? P + off[v] + k : kZero8, tile + a * SB * 32 + v * 512);
+        }
+    }
+    __device__ void advance(int) {}
+};
+
+// The filter tap and channel of a wave's K tile (k = (ky, kx, channel), tiles
+// within one tap), advanced without a division.
+struct KsTap {
+    int ky, kx, c, C, kw;
+    __device__ void init(int kb, int C_, int kw_) {
+        C = C_;
+        kw = kw_;
+        const int tap = kb / C;
+        c = kb - tap * C;
+        ky = tap / kw;
+        kx = tap - ky * kw;
+    }
+    __device__ void advance(int by) {
+        c += by;
+        while (c >= C) {
+            c -= C;
+            if (++kx == kw) {
+                kx = 0;
+                ++ky;
+            }
+        }
+    }
+};
+
+// A of a convolution's forward: rows = output pixels (as DmaConvA).
+struct KsConvA {
+    ConvGeom g;
+    KsTap t;
+    int iy0[4], ix0[4], koff;
+    int64_t base[4];
+    __device__ void init(const GemmDesc& d, bool, int r0, int R, int kb, int lane) {
+        g = d.g;
+        t.init(kb, g.Ci, g.kw);
+        koff = 8 * ((lane & 3) ^ ((lane >> 4) & 3));
+        const int hw = g.Ho * g.Wo;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int gr = r0 + 16 * v + (lane >> 2);
+            const int b = gr / hw, rem = gr - b * hw, oy = rem / g.Wo, ox = rem - oy * g.Wo;
+            iy0[v] = gr < R ? oy * g.stride - g.pad : -(1 << 20);  // (outside the map at every tap)
+            ix0[v] = ox * g.stride - g.pad;
+            base[v] = (((int64_t)b * g.H + iy0[v]) * g.W + ix0[v]) * g.Ci + koff;
+        }
+    }
+    template <int NB>
+    __device__ void copy(const bf16_t* X, int, int, bf16_t* tile) const {
+        const int add = (t.ky * g.W + t.kx) * g.Ci + t.c;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const bool in = (unsigned)(iy0[v] + t.ky) < (unsigned)g.H && (unsigned)(ix0[v] + t.kx) < (unsigned)g.W;
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+                ks_copy16(in ? X + base[v] + add + 32 * a : kZero8, tile + a * SB * 32 + v * 512);
+        }
+    }
+    __device__ void advance(int by) { t.advance(by); }
+};
+
+// A of a convolution's input gradient: rows = input pixels, strides 1 and 2 (as LdConvDx).
+struct KsConvDx {
+    ConvGeom g;
+    KsTap t;
+    int iy[4], ix[4], koff, sh;
+    int64_t base[4];
+    __device__ void init(const GemmDesc& d, bool, int r0, int R, int kb, int lane) {
+        g = d.g;
+        t.init(kb, g.Co, g.kw);
+        sh = g.stride - 1;
+        koff = 8 * ((lane & 3) ^ ((lane >> 4) & 3));
+        const int hw = g.H * g.W;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int gr = r0 + 16 * v + (lane >> 2);
+            const int b = gr / hw, rem = gr - b * hw, y = rem / g.W;
+            iy[v] = gr < R ? y + g.pad : -(1 << 20);  // (outside the map at every tap)
+            ix[v] = rem - y * g.W + g.pad;
+            base[v] = (int64_t)b * g.Ho * g.Wo * g.Co + koff;
+        }
+    }
+    template <int NB>
+    __device__ void copy(const bf16_t* DY, int, int, bf16_t* tile) const {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int ty = iy[v] - t.ky, tx = ix[v] - t.kx, oy = ty >> sh, ox = tx >> sh;
+            const bool in = ty >= 0 && tx >= 0 && ((ty | tx) & sh) == 0 && oy < g.Ho && ox < g.Wo;
+            const int64_t o = base[v] + (int64_t)((oy * g.Wo + ox) * g.Co + t.c);
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+                ks_copy16(in ? DY + o + 32 * a : kZero8, tile + a * SB * 32 + v * 512);
+        }
+    }
+    __device__ void advance(int by) { t.advance(by); }
+};
+
+// k-major operand, a [64 k][64 rows] tile for the transpose reads.  A k row is
+// 128 bytes, so rows k and k + 2 share LDS banks: the 64-byte halves of rows with
+// bit 1 of k set are swapped, and the four k rows of half a wave's read fall in
+// distinct 64-byte bank groups.
+__device__ __forceinline__ int ks_kr_idx(int k, int r) { return k * SB + (r ^ ((k & 2) << 4)); }
+struct KsKR {
+    int64_t off, ld;  // element offset of the lane's chunk at its first k row; elements between k rows
+    int sub;
+    bool ok;
+    __device__ void init(const GemmDesc& d, bool, int r0, int R, int, int lane) {
+        place(d.ldb, r0, R, lane);
+    }
+    __device__ void place(int64_t ld_, int r0, int R, int lane) {
+        ld = ld_;
+        sub = lane >> 3;
+        const int r = r0 + 8 * ((lane & 7) ^ ((sub & 2) << 1));
+        ok = r < R;
+        off = (int64_t)sub * ld + r;
+    }
+    template <int NB>
+    __device__ void copy(const bf16_t* P, int kb, int kend, bf16_t* tile) const {
+        const bf16_t* p = P + off + (int64_t)kb * ld;
+#pragma unroll
+        for (int v = 0; v < 8; ++v)
+            ks_copy16(ok && kb + sub + 8 * v < kend ? p + (int64_t)8 * v * ld : kZero8, tile + v * 512);
+    }
+    __device__ void advance(int) {}
+};
+// B of a convolution's input gradient: rows = ci, k = (ky, kx, co) of W[co][ky][kx][ci].
+struct KsConvDxW : KsKR {
+    KsTap t;
+    int Ci;
+    __device__ void init(const GemmDesc& d, bool, int r0, int R, int kb, int lane) {
+        Ci = d.g.Ci;
+        t.init(kb, d.g.Co, d.g.kw);
+        place((int64_t)d.g.kh * d.g.kw * Ci, r0, R, lane);
+    }
+    template <int NB>
+    __device__ void copy(const bf16_t* P, int, int, bf16_t* tile) const {
+        KsKR::copy<NB>(P + (int64_t)(t.ky * t.kw + t.kx) * Ci, t.c, t.C, tile);
+    }
+    __device__ void advance(int by) { t.advance(by); }
+};
+
+// Adds the waves' accumulators (Cs[wave][64][64]) and runs the epilogue (four-
+// column form, no fused SGD).  A thread takes columns c4 and c4 + 32 of a row and
+// walks the two with one copy of the epilogue's code (times as with drain_tile and
+// its sixteen copies, at half the code: 9-11 KB a kernel instead of 20).
+template <int NW, bool ORD>
+__device__ __forceinline__ void ks_drain(const GemmDesc& d, float* Cs, const TileJob& job, int M, int tid) {
+    const int c4 = (tid & 7) * 4, n0 = job.n0 + c4;
+    f32x4 csum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll 1
+    for (int lr = tid >> 3; lr < SB; lr += 8 * NW) {
+        const int row = job.m0 + lr;
+        const bool whole = job.S == 1 && row < M;
+        f32x4 v0, v1, b0 = {0.f, 0.f, 0.f, 0.f}, b1 = b0;
+        EpiIn4 e0, e1;
+        if (whole && n0 < d.N) {
+            e0 = epi_load4<false>(d, row, n0);
+            if (d.bias)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) b0[q] = d.bias[n0 + q];
+        }
+        if (whole && n0 + 32 < d.N) {
+            e1 = epi_load4<false>(d, row, n0 + 32);
+            if (d.bias)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) b1[q] = d.bias[n0 + 32 + q];
+        }
+        const f32x4* c = reinterpret_cast<const f32x4*>(Cs + lr * SB + c4);
+        constexpr int W = SB * SB / 4;  // between two waves' tiles
+        auto sum = [&](const f32x4* c) {
+            if constexpr (ORD) {  // the order of splitk_reduce, or of a consumer that takes the slices one by one
+                f32x4 v = c[0];
+                if (NW == 8 && !d.defer_reduce)
+                    v += (c[W] + c[2 * W]) + (c[3 * W] + c[4 * W]);
+                else
+#pragma unroll
+                    for (int z = 1; z < (NW == 8 ? 5 : 4); ++z) v += c[z * W];
+                if constexpr (NW == 8)
+#pragma unroll
+                    for (int z = 5; z < 8; ++z) v += c[z * W];
+                return v;
+            } else {
+                f32x4 v = (c[0] + c[W]) + (c[2 * W] + c[3 * W]);
+                if constexpr (NW == 8) v += (c[4 * W] + c[5 * W]) + (c[6 * W] + c[7 * W]);
+                return v;
+            }
+        };
+        v0 = sum(c);
+        v1 = sum(c + 8);
+        if (row >= M) continue;
+        if (job.S > 1) {
+            float* o = d.ws + ((int64_t)job.zt * d.M + row) * d.N + n0;
+            if (n0 < d.N) *reinterpret_cast<f32x4*>(o) = v0;
+            if (n0 + 32 < d.N) *reinterpret_cast<f32x4*>(o + 32) = v1;
+            continue;
+        }
+        f32x4 v = v0 + b0 + e0.resid;
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            if (n0 + 32 * h >= d.N) break;
+            v = epi_store4<false>(d, row, n0 + 32 * h, v, e0);
+            if (h == 0) {
+                csum[0] += v;
+                e0 = e1;
+                v = v1 + b1 + e1.resid;
+            } else {
+                csum[1] += v;
+            }
+        }
+    }
+    if (d.colpart) {  // uniform; a wave's rows by shuffles, the waves' sums in LDS
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int off = 8; off < 64; off <<= 1) csum[h][q] += __shfl_xor(csum[h][q], off);
+        __syncthreads();
+        if ((tid & 63) < 8) {
+            *reinterpret_cast<f32x4*>(&Cs[(tid >> 6) * SB + c4]) = csum[0];
+            *reinterpret_cast<f32x4*>(&Cs[(tid >> 6) * SB + c4 + 32]) = csum[1];
+        }
+        __syncthreads();
+        if (tid < SB && job.n0 + tid < d.N) {
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) t += Cs[w * SB + tid];
+            d.colpart[(int64_t)job.mt * d.N + job.n0 + tid] = t;
+        }
+    }
+}
+
+// NSEG = 1: B is k-major (KsKR, KsConvDxW); NSEG = 2, 3: B is row-major with a low part.
+// ORD (d.ordered): wave w takes the K slice w of d.ordered in a row, not every NW-th
+// tile, and ks_drain adds the slices as the pass after a split-K product does.
+template <int NSEG, int NW, bool ORD, class LA, class LB>
+__global__ void __launch_bounds__(64 * NW, 2) gemm_ks_kernel(const GemmDesc d) {
+    constexpr bool CMP = NSEG > 1;
+    constexpr int KT = CMP ? 32 : 64, NB = KT / 32;
+    if (!CMP) __builtin_amdgcn_s_setprio(2);  // on the input-gradient chain (see gemm_rk_krt_dma_kernel)
+    __shared__ __attribute__((aligned(1024))) bf16_t smem[NW][kKsStage];
+    static_assert(sizeof(smem) >= NW * SB * SB * 4, "the accumulators meet in the stages");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = d.Mdev ? min(d.M, *d.Mdev) : d.M;
+    const int K = d.K;
+    if (d.prof_snap && (blockIdx.x | blockIdx.y | blockIdx.z) == 0 && tid == 0) {
+        d.prof_snap[0] = M;
+        d.prof_snap[1] = K;
+    }
+    TileJob job;
+    if (!map_tile<SB, SB>(d, M, d.nseg * gemm_kseg(d, K), job)) return;  // uniform for the whole workgroup
+    // K tiles of the product and of a slice; the wave's first, its stride and its end
+    const int nkt = (K + KT - 1) / KT, nsl = ORD ? d.ordered : job.S, kct = (nkt + nsl - 1) / nsl;
+    const int tbeg = (ORD ? wave : job.zt) * kct, tend = min(nkt, tbeg + kct);
+    constexpr int STEP = ORD ? 1 : NW;
+    int t = ORD ? tbeg : tbeg + wave;
+
+    LA la;
+    LB lb;
+    la.init(d, true, job.m0, M, t * KT, lane);
+    lb.init(d, false, job.n0, d.N, t * KT, lane);
+    bf16_t* st = smem[wave];
+
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    auto copy_tile = [&]() {  // K tile t
+        la.template copy<NB>(d.A, t * KT, K, st);
+        if constexpr (NSEG == 3) la.template copy<NB>(d.A2, t * KT, K, st + 2048);
+        lb.template copy<NB>(d.B, t * KT, K, st + 4096);
+        if constexpr (CMP) lb.template copy<NB>(d.B2, t * KT, K, st + 6144);
+        la.advance(STEP * KT);
+        lb.advance(STEP * KT);
+    };
+    const int lrow = lane & 31, lc = lane >> 5;
+    auto frag = [&](const bf16_t* T, int row, int ks) {
+        return *reinterpret_cast<const bf16x8_t*>(&T[row * 32 + 8 * ((2 * ks + lc) ^ ((row >> 2) & 3))]);
+    };
+    int tr[2];  // transpose reads of the lane: k block 0, row blocks 0 and 32
+    {
+        const int g = lane >> 4, q = lane & 15, k = 8 * (g >> 1) + (q >> 2), r = 16 * (g & 1) + 4 * (q & 3);
+        tr[0] = ks_kr_idx(k, r);
+        tr[1] = ks_kr_idx(k, r + 32);
+    }
+    if (t < tend) copy_tile();
+    while (t < tend) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // the wave's own copy has landed
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        bf16x8_t a[KT / 16][2], b[KT / 16][2], al[KT / 16][2], bl[KT / 16][2];
+#pragma unroll
+        for (int ks = 0; ks < KT / 16; ++ks)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if constexpr (CMP) {
+                    a[ks][i] = frag(st, 32 * i + lrow, ks);
+                    b[ks][i] = frag(st + 4096, 32 * i + lrow, ks);
+                    bl[ks][i] = frag(st + 6144, 32 * i + lrow, ks);
+                    if constexpr (NSEG == 3) al[ks][i] = frag(st + 2048, 32 * i + lrow, ks);
+                } else {
+                    a[ks][i] = frag(st + (ks >> 1) * 2048, 32 * i + lrow, ks & 1);
+                    // (bit 1 of k is the same four k rows on)
+                    b[ks][i] = frag_tr(st + 4096, make_int2(tr[i], tr[i] + 4 * SB), ks * 16 * SB);
+                }
+            }
+        __builtin_amdgcn_s_waitcnt(0);  // the fragments are in registers: the stage may be overwritten
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        t += STEP;
+        if (t < tend) copy_tile();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KT / 16; ++ks)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+                    if constexpr (CMP)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], bl[ks][j], acc[i][j], 0, 0, 0);
+                    if constexpr (NSEG == 3)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+                }
+    }
+    // the waves' sums, each in its own stage
+    float* Cs = reinterpret_cast<float*>(&smem[0][0]);
+    float* mine = Cs + wave * SB * SB;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                mine[(i * 32 + (r >> 2) * 8 + lc * 4 + (r & 3)) * SB + j * 32 + lrow] = acc[i][j][r];
+    __syncthreads();
+    ks_drain<NW, ORD>(d, Cs, job, M, tid);
+}
+
 // Sums the split-K partials and runs the epilogue; four columns per thread
 // when N % 4 == 0, with the slices loaded four at a time.
 __global__ void __launch_bounds__(256) splitk_reduce(const GemmDesc d) {
@@ -1907,6 +2303,41 @@ void launch_rk_krt(const GemmDesc& d, hipStream_t s) {
     dd.prof_snap = prof_snap(h);
     dim3 grid((d.N + BN - 1) / BN, (d.M + BM - 1) / BM, d.splits);
     hipExtLaunchKernelGGL((gemm_rk_krt_dma_kernel<kDgradKT, kDgradNST>), grid, dim3(NT), 0, s, ea, eb, 0, dd);
+    prof_end_ext(h);
+}
+
+template <int NSEG, class LA, class LB>
+void launch_ks(const GemmDesc& d, hipStream_t s) {
+    ProfInfo pi;
+    pi.kind = PROF_GEMM;
+    pi.M = d.M; pi.N = d.N; pi.K = d.K; pi.nseg = d.nseg;
+    pi.Mdev = d.Mdev; pi.Kdev = d.Kdev;
+    hipEvent_t ea, eb;
+    constexpr bool conv = !std::is_same<LA, KsRK>::value;
+    const char* name = NSEG == 3 ? (conv ? "gemm_ks_kernel<3, conv>" : "gemm_ks_kernel<3>")
+                                 : NSEG == 2 ? (conv ? "gemm_ks_kernel<2, conv>" : "gemm_ks_kernel<2>")
+                                             : (conv ? "gemm_ks_kernel<1, conv>" : "gemm_ks_kernel<1>");
+    const int h = prof_begin_ext(name, pi, &ea, &eb);
+    GemmDesc dd = d;
+    dd.prof_snap = prof_snap(h);
+    dim3 grid((d.N + SB - 1) / SB, (d.M + SB - 1) / SB, d.splits);
+    // Eight waves where the launch leaves no CU a second workgroup (device step at
+    // batch 16 176 us against 178).  Packed rows only up to 256: their launches run beside
+    // the weight gradients, whose LDS leaves no room for 128 KB (transformer, both
+    // directions on small tiles, at batch 2 1712 against 1781 us, at 5 2136 against 1998).
+    const bool eight = d.Mdev ? d.M <= 256 : (int64_t)grid.x * grid.y * grid.z <= 256;
+    if (d.ordered) {
+        dd.ordered = d.splits;
+        dd.splits = 1;
+        grid.z = 1;
+        if (d.splits > 4)
+            hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 8, true, LA, LB>), grid, dim3(512), 0, s, ea, eb, 0, dd);
+        else
+            hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 4, true, LA, LB>), grid, dim3(256), 0, s, ea, eb, 0, dd);
+    } else if (eight)
+        hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 8, false, LA, LB>), grid, dim3(512), 0, s, ea, eb, 0, dd);
+    else
+        hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 4, false, LA, LB>), grid, dim3(256), 0, s, ea, eb, 0, dd);
     prof_end_ext(h);
 }
 
@@ -2056,6 +2487,64 @@ fo_status launch_splitk_sum_multi(const SplitJobs& jobs, hipStream_t s) {
     return FO_OK;
 }
 
+// The four-column epilogue: N and every leading dimension multiples of 4, fp32
+// operands 16-byte and bf16 operands 8-byte aligned.
+static bool vec_epilogue(const GemmDesc& d) {
+    auto al = [](const void* p, uintptr_t m) { return p == nullptr || ((uintptr_t)p & (m - 1)) == 0; };
+    bool v = d.N % 4 == 0 && al(d.ws, 16) && al(d.Cf, 16) && al(d.resid, 16) && al(d.Cb, 8) && al(d.Cb2, 8) &&
+             al(d.dact_out, 8) && al(d.mask, 8) && al(d.dact, 8) && al(d.colpart, 4) && al(d.sgd_theta, 16) &&
+             al(d.sgd_hi, 8) && al(d.sgd_lo, 8);
+    if (d.Cf) v = v && d.ldcf % 4 == 0;
+    if (d.resid) v = v && d.ldr % 4 == 0;
+    if (d.Cb) v = v && d.ldcb % 4 == 0;
+    if (d.dact_out || d.mask || d.dact) v = v && d.ldm % 4 == 0;
+    return v;
+}
+// What gemm_ks_kernel takes: aligned compensated products of row-major operands
+// and convolution forwards, and aligned input gradients (row-major times k-major,
+// convolutions of stride 1 or 2) without low parts.
+static bool ks_form(const GemmDesc& d) {
+    if (d.sgd_theta || !vec_epilogue(d)) return false;
+    auto al16 = [](const void* p) { return p == nullptr || ((uintptr_t)p & 15) == 0; };
+    if (d.Kdev || !al16(d.A) || !al16(d.A2) || !al16(d.B) || !al16(d.B2)) return false;
+    const bool rk_a = d.amode == OP_RK && d.lda % 8 == 0 && d.K % 8 == 0;
+    const bool rk_b = d.bmode == OP_RK && d.ldb % 8 == 0 && d.K % 8 == 0;
+    if (d.nseg > 1) return rk_b && (rk_a || (d.amode == OP_CONV_FWD && d.g.Ci % 32 == 0));
+    if (d.amode == OP_RK && d.bmode == OP_KR) return rk_a && d.ldb % 8 == 0 && d.N % 8 == 0;
+    return d.amode == OP_CONV_DX && d.bmode == OP_CONV_DXW && d.g.Co % 64 == 0 && d.g.Ci % 8 == 0 &&
+           (d.g.stride == 1 || d.g.stride == 2);
+}
+// Where the line lies (a step, small tiles against 128 x 128):
+//  - ordered sums of 4 to 8 slices whose 64 x 64 tiles give (nearly) every CU one:
+//    a workgroup then holds all slices of its tile (VGG-16 at batch 64; with 64
+//    tiles, as ResNet-18 has, 858 us a step against 640 on unordered slices).
+//  - static sizes, up to 256 tiles of 128 x 128; past that the 128 x 128
+//    kernels fill the chip and read half the operand bytes.  An N of 64 leaves
+//    half of a 128-wide tile idle (device step 326 against 280 us).
+//  - packed rows (the row count on the device, on average 0.63 of M), input
+//    gradients: up to M = 1536.  Transformer at batch 2, 5, 8 and 12: 2497,
+//    2546, 2609 and 2737 against 2193, 2339, 2506 and 2688 us; at 16 (M = 2048) small
+//    tiles lost, their launches beside the weight gradients being bound by bytes read.
+//    Compensated forwards keep the 128 x 128 tiles' order of summation.
+int gemm_tile(const GemmDesc& d) {
+    if (!ks_form(d)) return BM;
+    const int64_t big = cdiv(d.M, BM) * cdiv(d.N, BN), small = cdiv(d.M, SB) * cdiv(d.N, SB);
+    if (d.ordered) return !d.Mdev && d.splits >= 4 && d.splits <= 8 && small >= 192 && big <= 256 ? SB : BM;
+    if (d.Mdev) return d.nseg == 1 && d.M <= 1536 ? SB : BM;
+    return d.N <= SB || big <= 256 ? SB : BM;
+}
+int gemm_slices_left(const GemmDesc& d) { return d.ordered && gemm_tile(d) == SB ? 1 : d.splits; }
+// As many slices as fit one round of workgroups (one per CU with 64 x 64 tiles,
+// two with 128 x 128), each at least 256 long (device step at batch 64 with one, two
+// workgroups per CU: 278 and 298 us).
+int gemm_splits(const GemmDesc& d, int maxs, int64_t ws_floats) {
+    const int t = gemm_tile(d);
+    const int64_t tiles = cdiv(d.M, t) * cdiv(d.N, t);
+    int64_t s = std::min<int64_t>({maxs, (t == SB ? 256 : 512) / tiles, ws_floats / ((int64_t)d.M * d.N)});
+    s = std::min<int64_t>(s, d.K / 256);
+    return (int)std::max<int64_t>(1, s);
+}
+
 fo_status gemm(const GemmDesc& d, hipStream_t s) {
     FO_CHECK(d.M > 0 && d.N > 0 && d.K > 0, "gemm: empty problem %dx%dx%d", d.M, d.N, d.K);
     FO_CHECK(d.splits >= 1 && (d.splits == 1 || d.ws != nullptr), "gemm: split-K needs a workspace");
@@ -2075,20 +2564,8 @@ fo_status gemm(const GemmDesc& d, hipStream_t s) {
         FO_CHECK(d.B2 && (d.nseg == 2 || d.A2), "gemm: compensated product needs its low parts");
         FO_CHECK(!d.Kdev, "gemm: compensated product needs a static K");
     }
-    // four-column epilogue: N and every leading dimension multiples of 4, fp32
-    // operands 16-byte and bf16 operands 8-byte aligned
     GemmDesc dv = d;
-    {
-        auto al = [](const void* p, uintptr_t m) { return p == nullptr || ((uintptr_t)p & (m - 1)) == 0; };
-        bool v = d.N % 4 == 0 && al(d.ws, 16) && al(d.Cf, 16) && al(d.resid, 16) && al(d.Cb, 8) && al(d.Cb2, 8) &&
-                 al(d.dact_out, 8) && al(d.mask, 8) && al(d.dact, 8) && al(d.colpart, 4) && al(d.sgd_theta, 16) &&
-                 al(d.sgd_hi, 8) && al(d.sgd_lo, 8);
-        if (d.Cf) v = v && d.ldcf % 4 == 0;
-        if (d.resid) v = v && d.ldr % 4 == 0;
-        if (d.Cb) v = v && d.ldcb % 4 == 0;
-        if (d.dact_out || d.mask || d.dact) v = v && d.ldm % 4 == 0;
-        dv.vec_epi = v ? 1 : 0;
-    }
+    dv.vec_epi = vec_epilogue(d) ? 1 : 0;
     const int a = d.amode, b = d.bmode;
     // aligned variant: every contiguous dimension a multiple of 8 and 16-byte rows
     auto al16 = [](const void* p) { return p == nullptr || ((uintptr_t)p & 15) == 0; };
@@ -2108,9 +2585,15 @@ fo_status gemm(const GemmDesc& d, hipStream_t s) {
     // an unsplit aligned product of two k-major operands (a weight gradient)
     // runs as a group of one on the kernel with copies into LDS
     if (a == OP_KR && b == OP_KR && al && d.splits == 1 && d.nseg == 1 && !d.colpart) return gemm_group(&d, 1, s, 0);
+    dv.tile = gemm_tile(d);
     // (two stages and two workgroups per CU beat deeper rings at one per CU, and
     // 256 x 128 tiles with a three-stage ring at one per CU on these products)
-    if (a == OP_RK && b == OP_RK && al && d.nseg > 1 && !d.Kdev)
+    if (dv.tile == SB) {
+        if (a == OP_CONV_DX) launch_ks<1, KsConvDx, KsConvDxW>(dv, s);
+        else if (d.nseg == 1) launch_ks<1, KsRK, KsKR>(dv, s);
+        else if (a == OP_CONV_FWD) d.nseg == 3 ? launch_ks<3, KsConvA, KsRK>(dv, s) : launch_ks<2, KsConvA, KsRK>(dv, s);
+        else d.nseg == 3 ? launch_ks<3, KsRK, KsRK>(dv, s) : launch_ks<2, KsRK, KsRK>(dv, s);
+    } else if (a == OP_RK && b == OP_RK && al && d.nseg > 1 && !d.Kdev)
         d.nseg == 3 ? launch_comp<3>(dv, s) : launch_comp<2>(dv, s);
     else if (a == OP_RK && b == OP_RK) al ? launch<OP_RK, OP_RK, true>(dv, s) : launch<OP_RK, OP_RK>(dv, s);
     else if (a == OP_RK && b == OP_KR && al && d.nseg == 1 && !d.Kdev) launch_rk_krt(dv, s);
@@ -2131,7 +2614,7 @@ fo_status gemm(const GemmDesc& d, hipStream_t s) {
         return FO_EINVAL;
     }
     FO_LAUNCHED();
-    if (d.splits > 1 && !d.defer_reduce) {
+    if (gemm_slices_left(d) > 1 && !d.defer_reduce) {
         int64_t total = (int64_t)d.M * d.N;
         if (d.N % 4 == 0) total /= 4;
         int grid = (int)std::min<int64_t>(cdiv(total, 256), 4096);

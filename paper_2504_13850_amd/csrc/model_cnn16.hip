@@ -50,9 +50,9 @@ constexpr int kIn = 64, kHW = 16;  // server input: [B][64][16][16]
 
 struct Conv {
     int cin, cout, k, stride, pad, H, W, Ho, Wo;
+    int fsplits, dsplits;       // K slices of the forward and of the input gradient
     int64_t w, b;               // parameter offsets (b < 0: no bias)
     int64_t g, be;              // batch-norm scale / shift offsets (< 0: none)
-    int fsplits, dsplits;       // K slices of the forward and of the input gradient
     // activations
     bf16_t *yh, *yl;            // VGG: post-ReLU output (hi, lo)
     float *z, *mean, *rstd;     // ResNet: pre-norm output and its batch statistics
@@ -353,7 +353,9 @@ GemmDesc conv_fwd_desc(const fo_model* m, const Conv& c, int B, const bf16_t* xh
     d.bmode = OP_RK; d.B = m->w16 + c.w; d.B2 = m->w16lo + c.w; d.ldb = d.K;
     d.nseg = xl ? 3 : 2;
     d.g = geom(c, B);
-    d.splits = c.fsplits; d.ws = static_cast<const Plan*>(m->plan)->splitws;
+    d.ws = static_cast<const Plan*>(m->plan)->splitws;
+    d.splits = c.fsplits;
+    d.ordered = 1;
     return d;
 }
 
@@ -410,7 +412,9 @@ fo_status conv_dgrad(fo_model* m, const Conv& c, int B, const bf16_t* dzb, const
     d.resid = resid; d.ldr = c.cin;
     d.Cf = outf; d.ldcf = c.cin;
     d.Cb = outb; d.ldcb = c.cin;
-    d.splits = c.dsplits; d.ws = static_cast<const Plan*>(m->plan)->splitws;
+    d.ws = static_cast<const Plan*>(m->plan)->splitws;
+    d.splits = c.dsplits;
+    d.ordered = 1;
     return gemm(d, m->stream);
 }
 
@@ -422,6 +426,7 @@ fo_status fc_fwd(fo_model* m, const Fc& f, int B, const bf16_t* xh, const bf16_t
     d.amode = OP_RK; d.A = xh; d.A2 = xl; d.lda = f.in;
     d.bmode = OP_RK; d.B = m->w16 + f.w; d.B2 = m->w16lo + f.w; d.ldb = f.in;
     d.nseg = xl ? 3 : 2;
+    d.ordered = 1;
     d.bias = m->params + f.b;
     d.act = relu ? ACT_RELU : ACT_NONE;
     d.Cf = outf; d.ldcf = f.out;
@@ -448,6 +453,7 @@ fo_status fc_bwd(fo_model* m, Plan* P, const Fc& f, int B, const float* dyf, con
         d.M = B; d.N = f.in; d.K = f.out;
         d.amode = OP_RK; d.A = dyb; d.lda = f.out;
         d.bmode = OP_KR; d.B = m->w16 + f.w; d.ldb = f.in;
+        d.ordered = 1;
         d.mask = mask; d.ldm = f.in;
         d.Cf = dxf; d.ldcf = f.in;
         d.Cb = dxb; d.ldcb = f.in;
@@ -538,7 +544,7 @@ fo_status step_resnet(fo_model* m, Plan* P, int B, const int32_t* labels) {
             d.Cf = c.z; d.ldcf = c.cout;
             d.defer_reduce = true;
             TRY(gemm(d, s));
-            return launch_bn_fwd_stats(P->splitws, d.splits, c.z, rows, c.cout, c.part, s);
+            return launch_bn_fwd_stats(P->splitws, gemm_slices_left(d), c.z, rows, c.cout, c.part, s);
         };
         auto bn_apply = [&](Conv& c, const float* resf, const bf16_t* resh, const bf16_t* resl, bool relu, float* yf,
                             bf16_t* yh, bf16_t* yl) {

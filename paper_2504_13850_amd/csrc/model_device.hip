@@ -57,14 +57,13 @@ struct Plan {
     float *da, *dxi, *dh2f, *dh1;
     bf16_t *dab, *dh2b;
     float *splitws, *colws, *slws, *w1part;
-    int split_af, split_aw, split_ad, split_2w;
+    int split_aw, split_2w;  // K slices of the two weight gradients
 };
 
-// K slices of a product: enough for about 512 workgroups over its output
-// tiles, at most max_s, each slice at least 256 long.  The weight gradients
-// here have five 128 x 128 tiles (64 x 576) over K = B * H * W pixels, so they
-// take up to 64 slices.
-int split_for(int M, int N, int K, int max_s = 8) {
+// K slices of a weight gradient: enough for about 512 workgroups over its output
+// tiles, at most max_s, each slice at least 256 long.  Five 128 x 128 tiles
+// (64 x 576) over K = B * H * W pixels, so up to 64 slices.
+int split_for(int M, int N, int K, int max_s) {
     int tiles = (int)(cdiv(M, 128) * cdiv(N, 128));
     int s = std::max(1, std::min(max_s, 512 / std::max(tiles, 1)));
     while (s > 1 && (int64_t)K / s < 256) --s;
@@ -213,7 +212,7 @@ ConvGeom geom(int B, int H) {
 
 // y = ReLU(b + conv3x3(x)) as a compensated implicit GEMM, NHWC (high, low) out
 fo_status conv_fwd(fo_model* m, const Plan* P, int B, int H, const bf16_t* xh, const bf16_t* xl, int64_t w, int64_t b,
-                   int splits, bf16_t* yh, bf16_t* yl) {
+                   bf16_t* yh, bf16_t* yl) {
     GemmDesc d;
     d.M = B * H * H; d.N = C; d.K = KK;
     d.amode = OP_CONV_FWD; d.A = xh; d.A2 = xl;
@@ -223,7 +222,8 @@ fo_status conv_fwd(fo_model* m, const Plan* P, int B, int H, const bf16_t* xh, c
     d.bias = m->params + b;
     d.act = ACT_RELU;
     d.Cb = yh; d.Cb2 = yl; d.ldcb = C;
-    d.splits = splits; d.ws = P->splitws;
+    d.ws = P->splitws;
+    d.splits = gemm_splits(d, 8, kSplitFloats);
     return gemm(d, m->stream);
 }
 
@@ -242,7 +242,7 @@ fo_status conv_wgrad(fo_model* m, const Plan* P, int B, int H, const bf16_t* dyb
 
 // dx = conv^T(dy) (fp32), times [mask > 0] when mask is set
 fo_status conv_dgrad(fo_model* m, const Plan* P, int B, int H, const bf16_t* dyb, int64_t w, const bf16_t* mask,
-                     int splits, float* dxf) {
+                     float* dxf) {
     GemmDesc d;
     d.M = B * H * H; d.N = C; d.K = KK;
     d.amode = OP_CONV_DX; d.A = dyb;
@@ -250,7 +250,8 @@ fo_status conv_dgrad(fo_model* m, const Plan* P, int B, int H, const bf16_t* dyb
     d.g = geom(B, H);
     d.mask = mask; d.ldm = C;
     d.Cf = dxf; d.ldcf = C;
-    d.splits = splits; d.ws = P->splitws;
+    d.ws = P->splitws;
+    d.splits = gemm_splits(d, 8, kSplitFloats);
     return gemm(d, m->stream);
 }
 
@@ -267,10 +268,8 @@ size_t ws_bytes(const fo_model* m) {
     add(4 * n1); add(4 * n1); add(4 * n0); add(4 * n0); // da, dxi, dh2f, dh1
     add(2 * n1); add(2 * n0);                           // dab, dh2b
     const int Bi = (int)B;
-    size_t sw = 0;
-    sw = std::max(sw, gemm_ws_bytes(Bi * H1 * H1, C, split_for(Bi * H1 * H1, C, 3 * KK)));
+    size_t sw = 4 * kSplitFloats;
     sw = std::max(sw, gemm_ws_bytes(C, KK, split_for(C, KK, Bi * H1 * H1, 64)));
-    sw = std::max(sw, gemm_ws_bytes(Bi * H1 * H1, C, split_for(Bi * H1 * H1, C, KK)));
     sw = std::max(sw, gemm_ws_bytes(C, KK, split_for(C, KK, Bi * H0 * H0, 64)));
     add(sw + 256);
     add(4 * colsum_ws_floats(Bi * H0 * H0, C));
@@ -296,14 +295,10 @@ fo_status init(fo_model* m) {
     P->g = a.take<float>((size_t)B * C); P->dz = a.take<float>((size_t)B * NCLS); P->dg = a.take<float>((size_t)B * C);
     P->da = a.take<float>(n1); P->dxi = a.take<float>(n1); P->dh2f = a.take<float>(n0); P->dh1 = a.take<float>(n0);
     P->dab = a.take<bf16_t>(n1); P->dh2b = a.take<bf16_t>(n0);
-    P->split_af = split_for(B * H1 * H1, C, 3 * KK);
     P->split_aw = split_for(C, KK, B * H1 * H1, 64);
-    P->split_ad = split_for(B * H1 * H1, C, KK);
     P->split_2w = split_for(C, KK, B * H0 * H0, 64);
-    size_t sw = 0;
-    sw = std::max(sw, gemm_ws_bytes(B * H1 * H1, C, P->split_af));
+    size_t sw = 4 * kSplitFloats;
     sw = std::max(sw, gemm_ws_bytes(C, KK, P->split_aw));
-    sw = std::max(sw, gemm_ws_bytes(B * H1 * H1, C, P->split_ad));
     sw = std::max(sw, gemm_ws_bytes(C, KK, P->split_2w));
     P->splitws = a.take<float>(sw / 4 + 64);
     P->colws = a.take<float>(colsum_ws_floats(B * H0 * H0, C));
@@ -335,12 +330,12 @@ fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
         hipLaunchKernelGGL(conv1_fwd, dim3(grid), dim3(256), 0, s, m->dev_in, prm + W1, prm + B1, P->h1h, P->h1l, B);
         FO_LAUNCHED();
     }
-    TRY(conv_fwd(m, P, B, H0, P->h1h, P->h1l, W2, B2, 1, P->h2h, P->h2l));
+    TRY(conv_fwd(m, P, B, H0, P->h1h, P->h1l, W2, B2, P->h2h, P->h2l));
     TRY(launch_maxpool_fwd(P->h2h, P->h2l, P->xih, P->xil, P->arg, B, H0, H0, C, s));
     hipLaunchKernelGGL(acts_out_nchw, dim3(H1 * H1 / 32, C / 32, B), dim3(256), 0, s, m->dev_in, P->xih, B);
     FO_LAUNCHED();
     // ---- forward of the auxiliary network on xi and the local loss f_d
-    TRY(conv_fwd(m, P, B, H1, P->xih, P->xil, WA, BA, P->split_af, P->ah, P->al));
+    TRY(conv_fwd(m, P, B, H1, P->xih, P->xil, WA, BA, P->ah, P->al));
     TRY(launch_gap_fwd(P->ah, P->al, P->g, B, H1 * H1, C, s));
     TRY(launch_small_linear_fwd(P->g, prm + WF, prm + BF, m->logits, B, C, NCLS, false, s));
     TRY(launch_xent(m->logits, m->dev_in, P->dz, m->loss, B, NCLS, s));
@@ -350,12 +345,12 @@ fo_status step(fo_model* m, const fo_acts* acts, const int32_t* labels) {
     TRY(launch_to_bf16(P->da, P->dab, (int64_t)rows1 * C, s));
     TRY(conv_wgrad(m, P, B, H1, P->dab, P->xih, WA, P->split_aw));
     TRY(launch_colsum(P->da, C, rows1, nullptr, C, grd + BA, P->colws, s));
-    TRY(conv_dgrad(m, P, B, H1, P->dab, WA, nullptr, P->split_ad, P->dxi));
+    TRY(conv_dgrad(m, P, B, H1, P->dab, WA, nullptr, P->dxi));
     // ---- backward of the device network (through the pool and conv2's ReLU)
     TRY(launch_maxpool_relu_bwd(P->dxi, P->arg, P->h2h, P->dh2f, P->dh2b, B, H0, H0, C, s));
     TRY(conv_wgrad(m, P, B, H0, P->dh2b, P->h1h, W2, P->split_2w));
     TRY(launch_colsum(P->dh2f, C, rows0, nullptr, C, grd + B2, P->colws, s));
-    TRY(conv_dgrad(m, P, B, H0, P->dh2b, W2, P->h1h, 1, P->dh1));  // times conv1's ReLU mask
+    TRY(conv_dgrad(m, P, B, H0, P->dh2b, W2, P->h1h, P->dh1));  // times conv1's ReLU mask
     {
         const int nblk = B * (H0 / W1_ROWS);
         hipLaunchKernelGGL(conv1_wgrad_partial, dim3(nblk), dim3(256), 0, s, m->dev_in, P->dh1, P->w1part);

@@ -107,6 +107,39 @@ def test_gemm_compensated_split_k(M, N, K, splits, with_alo):
     assert normwise(C.cpu().numpy(), av @ bv.T) <= 2e-5
 
 
+@pytest.mark.parametrize("M,N,K,form,splits", [
+    # 64 x 64 tiles with K dealt to the waves: one tile and its remainders, K
+    # shorter than a step, than one step per wave, ragged in a step, more slices
+    # than K tiles; then the last sizes on this side of the 128 x 128 tiles
+    (64, 64, 512, 3, 1), (65, 68, 520, 3, 1), (1, 4, 8, 3, 1), (63, 60, 40, 2, 1), (130, 200, 264, 3, 3),
+    (64, 64, 64, 2, 4), (64, 64, 512, 1, 1), (65, 72, 520, 1, 1), (1, 8, 8, 1, 1), (63, 56, 40, 1, 1),
+    (130, 200, 328, 1, 3), (64, 64, 64, 1, 4), (2048, 2048, 128, 3, 1), (2048, 2048, 128, 1, 1),
+    (4104, 64, 192, 1, 1)])
+def test_gemm_small_tiles(M, N, K, form, splits):
+    """form 3 and 2: compensated with and without A's low part; 1: k-major B.  fp32 sums of at most
+    3 x 520 products: bounds as in the tests above."""
+    torch = torch_cuda()
+    announce(f"gemm small tiles {M}x{N}x{K} form {form} s={splits}")
+    rng = np.random.default_rng(M + 3 * N + 7 * K + form)
+    al = bl = None
+    if form == 3:
+        ah, al, av = _split(rng, (M, K))
+    else:
+        ah, av = _bf16(rng, (M, K))
+    if form == 1:
+        bh, bv = _bf16(rng, (N, K))
+        bh = np.ascontiguousarray(bh.T)
+    else:
+        bh, bl, bv = _split(rng, (N, K))
+    C = torch.full((M + 1, N), 7.0, dtype=torch.float32, device="cuda")
+    ws = torch.empty(splits * M * N, dtype=torch.float32, device="cuda")
+    A.fo_gemm_bf16(M, N, K, 0, _dev16(ah), None if al is None else _dev16(al), K, int(form == 1), _dev16(bh),
+                   None if bl is None else _dev16(bl), N if form == 1 else K, C, N, splits, ws)
+    got = C.cpu().numpy()
+    assert normwise(got[:M], av @ bv.T) <= (1e-5 if form == 1 else 2e-5)
+    assert (got[M] == 7.0).all()  # nothing past the last row
+
+
 CONVS = [  # (Bn, H, Ci, Co, k, stride, pad)
     (2, 16, 64, 128, 3, 1, 1), (3, 8, 128, 256, 3, 1, 1), (2, 4, 256, 512, 3, 1, 1), (2, 2, 512, 512, 3, 1, 1),
     (32, 2, 512, 512, 3, 1, 1), (2, 16, 64, 128, 3, 2, 1), (4, 4, 256, 512, 3, 2, 1), (2, 16, 64, 128, 1, 2, 0),
