@@ -24,7 +24,8 @@
 // Activations are stored channel by channel, [C][ld], rows (sample, pixel)
 // contiguous and padded with zeros to a multiple of 16: a batch norm, a
 // convolution and a weight gradient (a product over rows) all read them
-// contiguously.
+// contiguously.  A step writes the padding that it reads (its place depends on
+// the batch size, so what is there is another step's data).
 #include "mbv3.h"
 #include "small_f32.h"
 
@@ -588,13 +589,11 @@ fo_status fused_init(fo_model* m, int max_batch, Fused** out) {
     Fused* F = new (std::nothrow) Fused();
     if (!F) return FO_ENOMEM;
     *out = F;
-    const size_t n = carve(F, std::min(max_batch, kFusedMax), &m->arena);
+    carve(F, std::min(max_batch, kFusedMax), &m->arena);
     if (!F->dz) {
         set_error("mbv3: workspace arena too small");
         return FO_ENOMEM;
     }
-    // padding rows are products' operands: finite from the start
-    FO_HIP(hipMemsetAsync(F->b[0].xh1, 0, n, m->stream));
     return FO_OK;
 }
 

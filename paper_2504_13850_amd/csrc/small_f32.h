@@ -127,7 +127,9 @@ __global__ void __launch_bounds__(LIN_T) linear_small(const Lin p) {
     if constexpr (EPI == E_SCALE) {
         const float z = in ? v + p.bias[on] : 0.f, s = hsig(z);
         p.out[o] = z;
-        if (!in) return;
+        // the maps' padding rows too (a is zero there): the projection's weight gradient
+        // multiplies them by zeros, and a shorter batch finds an earlier one's values there
+        if (b * p.hw >= p.ld2) return;
         const float* a = p.a2 + (int64_t)on * p.ld2 + b * p.hw;
         float* h = p.h + (int64_t)on * p.ld2 + b * p.hw;
         for (int q = 0; q < p.hw; q += 4) st4(h + q, ld4(a + q) * s);

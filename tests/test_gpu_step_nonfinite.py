@@ -1,0 +1,79 @@
+"""A step keeps nothing of the step before it but the parameters (and the
+momentum buffer).  Buffers padded to whole tiles are operands whose padding
+meets zeros, and 0 x NaN is NaN: after a step on a non-finite batch, whatever
+it left in the workspace, restoring the parameters with fo_model_write must
+give a model whose next step, on a shorter batch, is bit for bit the step of a
+new model (the other tests hold that step against the oracle)."""
+import numpy as np
+import pytest
+
+import fo_synth as S
+from tests.gpu_util import announce, to_dev, torch_cuda
+
+pytestmark = pytest.mark.gpu
+A = pytest.importorskip("paper_2504_13850_amd.api")
+
+# config: full batch, shorter batches (odd, not a multiple of 4 or 16, of another padded length)
+CASES = {2: (24, (5,)), 3: (24, (5,)), 4: (6, (3,)), 6: (18, (5,)), 7: (18, (5,)), 8: (6, (5,)),
+         9: (18, (15, 5)), 10: (32, (5, 3))}
+
+
+def _batch(torch, cid, B, sub):
+    x = S.make_acts(cid, 1, batch=B, sub=sub)[0]
+    x = to_dev(x.view(np.int16)).view(torch.bfloat16) if x.dtype == np.uint16 else to_dev(x)
+    lengths = to_dev(S.make_lengths(cid, 1, batch=B, sub=sub)[0]) if cid in (4, 7, 8) else None
+    return x, to_dev(S.make_labels(cid, 1, batch=B, sub=sub)[0]), lengths
+
+
+def _step(torch, model, cid, batch):
+    x, labels, lengths = batch
+    B = len(labels)
+    if cid == 6:
+        sent = torch.zeros((B, 64, 16, 16), dtype=torch.bfloat16, device="cuda")
+        A.fo_device_step(model, x, labels, B, sent)
+    else:
+        A.fo_server_step(model, (x, lengths, B), labels, 0)
+    out = {"loss": A.FO_BUF_LOSS, "logits": A.FO_BUF_LOGITS, "grads": A.FO_BUF_GRADS, "params": A.FO_BUF_PARAMS}
+    out = {k: A.fo_model_read(model, v) for k, v in out.items()}
+    if cid == 6:
+        out["sent"] = sent.float().cpu().numpy()
+    return out
+
+
+def _poison(torch, model, cid, theta, batch, how):
+    """A step that leaves NaN and infinities behind: a non-finite batch, or parameters
+    and a batch whose products overflow to +infinity (past every ReLU)."""
+    x, labels, lengths = batch
+    if how == "overflow":
+        A.fo_model_write(model, A.FO_BUF_PARAMS, np.abs(theta) * np.float32(1e18))
+        x = x.abs() * 1e18
+    else:
+        x = torch.full_like(x, float(how))
+    got = _step(torch, model, cid, (x, labels, lengths))
+    assert not all(np.isfinite(v).all() for v in got.values())
+
+
+# (the bf16 forwards split a value into two parts, and what overflows ends as zeros past their ReLUs)
+@pytest.mark.parametrize("cid,how", [(c, h) for c in sorted(CASES) for h in ("nan", "inf", "overflow")
+                                     if h != "overflow" or c in (1, 7, 8, 9, 10)])
+def test_no_trace_of_a_nonfinite_step(cid, how):
+    torch = torch_cuda()
+    full, shorter = CASES[cid]
+    theta = S.init_params(cid)
+    for B in shorter:
+        announce(f"config {cid} {how} batch {full}, then {B}")
+        batch = _batch(torch, cid, B, 70 + B)
+        model = A.fo_model_create(cid, full, theta, torch.cuda.current_stream())
+        fresh = A.fo_model_create(cid, full, theta, torch.cuda.current_stream())
+        try:
+            _poison(torch, model, cid, theta, _batch(torch, cid, full, 70), how)
+            A.fo_model_write(model, A.FO_BUF_PARAMS, theta)
+            if cid == 3:
+                A.fo_model_write(model, A.FO_BUF_MOMENTUM, np.zeros_like(theta))
+            got, want = _step(torch, model, cid, batch), _step(torch, fresh, cid, batch)
+            for k, v in want.items():
+                assert np.isfinite(v).all(), k
+                assert np.array_equal(got[k].view(np.uint32), v.view(np.uint32)), (k, B)
+        finally:
+            A.fo_model_destroy(model)
+            A.fo_model_destroy(fresh)
