@@ -32,7 +32,7 @@ struct Plan {
     float* p1;      // conv1 + ReLU, pooled [B][64][8][8]
     uint8_t* arg1;  // window position of its maximum (the first in row-major order)
     float* y2;      // conv2 + ReLU [B][64][8][8]
-    float* h;       // global average [64][ldb]
+    float* h;       // global average [64][ldb], samples only (its padding is not written)
     float* dh;      // its gradient
     float* dp1;     // gradient of p1 where p1 > 0
     float *part1, *part2;  // the weight gradients' shares [shares][64][9 Ci + 1], the bias last
@@ -380,13 +380,11 @@ fo_status init(fo_model* m) {
     Plan* P = new (std::nothrow) Plan();
     if (!P) return FO_ENOMEM;
     m->plan = P;
-    const size_t n = carve(P, m->max_batch, &m->arena);
+    carve(P, m->max_batch, &m->arena);
     if (!P->part2) {
         set_error("cnn32: workspace arena too small");
         return FO_ENOMEM;
     }
-    // the padding samples of h are operands (times zero) of the classifier's gradients: finite from the start
-    FO_HIP(hipMemsetAsync(P->h, 0, n, m->stream));
     return FO_OK;
 }
 

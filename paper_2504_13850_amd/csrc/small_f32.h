@@ -202,9 +202,9 @@ __global__ void __launch_bounds__(1024) small_head(const float* __restrict__ f1,
             const int e = t + 1024 * i;
             float s = 0.f, u = 0.f;
             if (e < C * F) {
-                for (int b = 0; b < nv; b += 2) {  // (an odd last sample is followed by padding or dz = 0)
+                for (int b = 0; b < nv; b += 2) {  // (samples only: padding may hold anything)
                     s = fmaf(dz[e / F][b], f[e % F][b], s);
-                    u = fmaf(b + 1 < nv ? dz[e / F][b + 1] : 0.f, f[e % F][b + 1], u);
+                    if (b + 1 < nv) u = fmaf(dz[e / F][b + 1], f[e % F][b + 1], u);
                 }
             } else if (e < C * F + C) {
                 for (int b = 0; b < nv; ++b) s += dz[e - C * F][b];

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 A = pytest.importorskip("paper_2504_13850_amd.api")
 
 # config: full batch, shorter batches (odd, not a multiple of 4 or 16, of another padded length)
-CASES = {2: (24, (5,)), 3: (24, (5,)), 4: (6, (3,)), 6: (18, (5,)), 7: (18, (5,)), 8: (6, (5,)),
+CASES = {1: (18, (15, 5)), 2: (24, (5,)), 3: (24, (5,)), 4: (6, (3,)), 6: (18, (5,)), 7: (18, (5,)), 8: (6, (5,)),
          9: (18, (15, 5)), 10: (32, (5, 3))}
 
 
