@@ -43,6 +43,22 @@ __device__ __forceinline__ f32x4 mfma(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// A product is kept as several running sums, added pairwise: the error of a sum
+// grows with the length of its chain of additions.  Four in the first
+// convolution and NP in the second and its input gradient (72 products each),
+// NPW per image in the weight gradients (32 and 64 pixels each; three taps at a
+// time, as two running sums of all nine leave no registers for a third wave per
+// SIMD).  Median error of the gradient over 24 batches of 16: 6.6e-8, with half
+// as many sums and one over all images 7.9e-8; the step takes 58.5 against 57.6 us.
+constexpr int NP = 8, NPW = 2;
+template <int N>
+__device__ __forceinline__ f32x4 pairwise(const f32x4* a) {
+    if constexpr (N == 1)
+        return a[0];
+    else
+        return pairwise<N / 2>(a) + pairwise<N / 2>(a + N / 2);
+}
+
 // Rows y0 - 1 .. y0 + NR of an image [C][H][H] into xs[C][NR + 2][H + 2] (LDS), zeros outside.
 template <int C, int H, int NR>
 __device__ __forceinline__ void stage(const float* __restrict__ x, int y0, float* xs) {
@@ -73,11 +89,11 @@ __global__ void __launch_bounds__(T) c1_fwd(const StepIn* __restrict__ in, const
     // the wave's two tiles: rows 2 wave, 2 wave + 1, columns 0-7 and 8-15
     const float* xr = xs + (2 * wave + (tok >> 3)) * W + (tok & 7);
     const float* wr = w + (int64_t)(co + tok) * 9 * C0 + 4 * g;
-    f32x4 acc[2][2];
+    f32x4 acc[2][4];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -87,11 +103,11 @@ __global__ void __launch_bounds__(T) c1_fwd(const StepIn* __restrict__ in, const
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
-                    acc[i][j & 1] = mfma(a[j], xr[(16 * s + 4 * g + j) * S + t / 3 * W + t % 3 + 8 * i], acc[i][j & 1]);
+                    acc[i][j] = mfma(a[j], xr[(16 * s + 4 * g + j) * S + t / 3 * W + t % 3 + 8 * i], acc[i][j]);
         }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const f32x4 z = (acc[i][0] + acc[i][1]) + bv;
+        const f32x4 z = pairwise<4>(acc[i]) + bv;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float v0 = fmaxf(z[k], 0.f), v1 = __shfl_xor(v0, 1), v2 = __shfl_xor(v0, 8), v3 = __shfl_xor(v1, 8);
@@ -127,9 +143,9 @@ __global__ void __launch_bounds__(T) c2_fwd(const float* __restrict__ p1, const 
     __syncthreads();
     const int px = 16 * wave + tok;
     const float* xr = xs + px / H1 * W + px % H1;
-    f32x4 acc[4];
+    f32x4 acc[NP];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NP; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         if (t + 1 < 9)
@@ -138,10 +154,12 @@ __global__ void __launch_bounds__(T) c2_fwd(const float* __restrict__ p1, const 
 #pragma unroll
         for (int s = 0; s < C1 / 16; ++s)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[j] = mfma(a[t & 1][s][j], xr[(16 * s + 4 * g + j) * S + t / 3 * W + t % 3], acc[j]);
+            for (int j = 0; j < 4; ++j) {
+                f32x4& c = acc[(4 * s + j) % NP];
+                c = mfma(a[t & 1][s][j], xr[(16 * s + 4 * g + j) * S + t / 3 * W + t % 3], c);
+            }
     }
-    const f32x4 z = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + bv;
+    const f32x4 z = pairwise<NP>(acc) + bv;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         float v = fmaxf(z[k], 0.f);
@@ -162,18 +180,18 @@ __device__ __forceinline__ float groups_sum(float v) {
     return v + __shfl_xor(v, 32);
 }
 
-// conv2 backward.  Blocks below B * 4: the input gradient of (image, 16 input
-// channels) through the pool's ReLU; the gradient of conv2's output is
-// [y2 > 0] dh / 64, formed while it is staged.  The rest: conv2's weight and
-// bias gradient of (share of the images, 16 output channels).
+// conv2 backward.  Blocks below 4 * shares (first: they are the longest): conv2's
+// weight and bias gradient of (share of the images, 16 output channels).  The
+// rest: the input gradient of (image, 16 input channels) through the pool's
+// ReLU; the gradient of conv2's output is [y2 > 0] dh / 64, formed while it is staged.
 __global__ void __launch_bounds__(T) c2_bwd(const float* __restrict__ p1, const float* __restrict__ y2,
                                             const float* __restrict__ dh, int ldb, const float* __restrict__ w,
                                             float* __restrict__ dp1, float* __restrict__ part, int B, int shares) {
     constexpr int W = H1 + 2, S = W * W;
     __shared__ float xs[C1 * S];
     const int lane = threadIdx.x & 63, tok = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
-    if ((int)blockIdx.x < 4 * B) {
-        const int b = blockIdx.x / 4, ci = blockIdx.x % 4 * 16;
+    if ((int)blockIdx.x >= 4 * shares) {
+        const int b = blockIdx.x / 4 - shares, ci = blockIdx.x % 4 * 16;
         const float* wr = w + ci + tok;
         float a[2][16];  // a tap's weights, loaded during the products of the one before
         auto load = [&](int t) {
@@ -200,18 +218,18 @@ __global__ void __launch_bounds__(T) c2_bwd(const float* __restrict__ p1, const 
         __syncthreads();
         const int px = 16 * wave + tok;
         const float* xr = xs + px / H1 * W + px % H1;
-        f32x4 acc[4];
+        f32x4 acc[NP];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < NP; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
             if (t + 1 < 9) load(t + 1);
 #pragma unroll
             for (int q = 0; q < 16; ++q)
-                acc[q % 4] = mfma(a[t & 1][q], xr[(16 * (q / 4) + 4 * g + q % 4) * S + (2 - t / 3) * W + 2 - t % 3],
-                                  acc[q % 4]);
+                acc[q % NP] = mfma(a[t & 1][q], xr[(16 * (q / 4) + 4 * g + q % 4) * S + (2 - t / 3) * W + 2 - t % 3],
+                                   acc[q % NP]);
         }
-        const f32x4 v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        const f32x4 v = pairwise<NP>(acc);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int64_t o = ((int64_t)b * C1 + ci + 4 * g + k) * P1 + px;
@@ -219,9 +237,9 @@ __global__ void __launch_bounds__(T) c2_bwd(const float* __restrict__ p1, const 
         }
         return;
     }
-    const int share = (blockIdx.x - 4 * B) / 4, co = blockIdx.x % 4 * 16;
+    const int share = blockIdx.x / 4, co = blockIdx.x % 4 * 16;
     f32x4 acc[9];
-    float bs = 0.f;
+    float bs[4] = {};
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* xr = xs + (16 * wave + tok) * S;
@@ -236,25 +254,35 @@ __global__ void __launch_bounds__(T) c2_bwd(const float* __restrict__ p1, const 
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 d[s][j] = d[s][j] > 0.f ? d1 : 0.f;
-                bs += d[s][j];
+                bs[s] += d[s][j];
             }
         }
         __syncthreads();
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int ky = 0; ky < 3; ++ky) {
+            f32x4 c[3][NPW];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int px = 16 * s + 4 * g + j;
-                const float* x = xr + px / H1 * W + px % H1;
+            for (int kx = 0; kx < 3; ++kx)
 #pragma unroll
-                for (int t = 0; t < 9; ++t) acc[t] = mfma(x[t / 3 * W + t % 3], d[s][j], acc[t]);
-            }
+                for (int s = 0; s < NPW; ++s) c[kx][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int px = 16 * s + 4 * g + j;
+                    const float* x = xr + (px / H1 + ky) * W + px % H1;
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx) c[kx][s % NPW] = mfma(x[kx], d[s][j], c[kx][s % NPW]);
+                }
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) acc[3 * ky + kx] += pairwise<NPW>(c[kx]);
+        }
     }
     float* o = part + ((int64_t)share * C2 + co + tok) * kRow2;
 #pragma unroll
     for (int t = 0; t < 9; ++t) st4(o + t * C1 + 16 * wave + 4 * g, acc[t]);
-    bs = groups_sum(bs);
-    if (wave == 0 && g == 0) o[9 * C1] = bs;
+    const float b4 = groups_sum((bs[0] + bs[1]) + (bs[2] + bs[3]));
+    if (wave == 0 && g == 0) o[9 * C1] = b4;
 }
 
 // conv1's weight and bias gradient: block = (share of the images, 16 output
@@ -269,7 +297,7 @@ __global__ void __launch_bounds__(T) c1_wgrad(const StepIn* __restrict__ in, con
     const int lane = threadIdx.x & 63, tok = lane & 15, g = lane >> 4, wave = threadIdx.x >> 6;
     const int share = blockIdx.x / 4, co = blockIdx.x % 4 * 16, cb = wave & 1, half = wave >> 1;
     f32x4 acc[9];
-    float bs = 0.f;
+    float bs[4] = {};
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const float* xr = xs + (16 * cb + tok) * S;
@@ -286,33 +314,43 @@ __global__ void __launch_bounds__(T) c1_wgrad(const StepIn* __restrict__ in, con
             for (int c = 0; c < 2; ++c) {
                 d[r][c] = dp1[q + r * H1 + c];
                 at[r][c] = arg1[q + r * H1 + c];
-                bs += d[r][c];
+                bs[r] += d[r][c];
             }
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 8; ++r)
+        for (int ky = 0; ky < 3; ++ky) {
+            f32x4 c[3][NPW];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v = at[r / 2][j / 2] == (r & 1) * 2 + (j & 1) ? d[r / 2][j / 2] : 0.f;
-                const float* x = xr + (8 * half + r) * W + 4 * g + j;
+            for (int kx = 0; kx < 3; ++kx)
 #pragma unroll
-                for (int t = 0; t < 9; ++t) acc[t] = mfma(x[t / 3 * W + t % 3], v, acc[t]);
-            }
+                for (int s = 0; s < NPW; ++s) c[kx][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float v = at[r / 2][j / 2] == (r & 1) * 2 + (j & 1) ? d[r / 2][j / 2] : 0.f;
+                    const float* x = xr + (8 * half + r + ky) * W + 4 * g + j;
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx) c[kx][r % NPW] = mfma(x[kx], v, c[kx][r % NPW]);
+                }
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) acc[3 * ky + kx] += pairwise<NPW>(c[kx]);
+        }
     }
-    bs = groups_sum(bs);
+    const float b4 = groups_sum((bs[0] + bs[1]) + (bs[2] + bs[3]));
     __syncthreads();
     float* o = part + ((int64_t)share * C1 + co + tok) * kRow1;
     f32x4* red = reinterpret_cast<f32x4*>(xs) + cb * 64 * 10 + lane;
     if (half) {
 #pragma unroll
         for (int t = 0; t < 9; ++t) red[64 * t] = acc[t];
-        red[64 * 9] = f32x4{bs, 0.f, 0.f, 0.f};
+        red[64 * 9] = f32x4{b4, 0.f, 0.f, 0.f};
     }
     __syncthreads();
     if (half) return;
 #pragma unroll
     for (int t = 0; t < 9; ++t) st4(o + t * C0 + 16 * cb + 4 * g, acc[t] + red[64 * t]);
-    if (cb == 0 && g == 0) o[9 * C0] = bs + red[64 * 9][0];
+    if (cb == 0 && g == 0) o[9 * C0] = b4 + red[64 * 9][0];
 }
 static_assert(2 * 64 * 10 * 4 <= C0 * (H0 + 2) * (H0 + 2), "partial sums of two waves in the image's LDS");
 

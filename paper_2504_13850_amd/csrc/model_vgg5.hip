@@ -181,9 +181,12 @@ __global__ void __launch_bounds__(256) v5_conv(const StepIn* __restrict__ in, co
     stage_image(in, b, xs);
     __syncthreads();
     const int px = 16 * wave + tok, at = px / HW * XP + px % HW;
-    f32x4 acc[4];
+    // sixteen running sums of 36 products each, added pairwise (the rounding error grows with their length)
+    f32x4 acc[CI / 16][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < CI / 16; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[s][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         if (t + 1 < 9)
@@ -193,10 +196,12 @@ __global__ void __launch_bounds__(256) v5_conv(const StepIn* __restrict__ in, co
         for (int s = 0; s < CI / 16; ++s)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                    a[t & 1][s][j], xs[(16 * s + 4 * g + j) * XS + at + t / 3 * XP + t % 3], acc[j], 0, 0, 0);
+                acc[s][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                    a[t & 1][s][j], xs[(16 * s + 4 * g + j) * XS + at + t / 3 * XP + t % 3], acc[s][j], 0, 0, 0);
     }
-    const f32x4 v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+    for (int s = 0; s < CI / 16; ++s) acc[s][0] = (acc[s][0] + acc[s][1]) + (acc[s][2] + acc[s][3]);
+    const f32x4 v = (acc[0][0] + acc[1][0]) + (acc[2][0] + acc[3][0]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) z[(co + 4 * g + i) * ld + b * HW * HW + px] = v[i];
 }

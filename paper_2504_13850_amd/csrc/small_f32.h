@@ -39,7 +39,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 // Y[n][b] = epi(sum_k W(n, k) X[k][b]) on v_mfma_f32_16x16x4_f32: a workgroup
 // takes 16 outputs of 32 samples, its eight waves an eighth of k each (the
 // products are a few hundred long and at most 80 workgroups wide, so their time
-// is the length of the k walk), added in order.  TR: W(n, k) = W[k][n].
+// is the length of the k walk), added in order.  A wave keeps two running sums
+// (the rounding error grows with their length).  TR: W(n, k) = W[k][n].
 enum Epi : int { E_RELU, E_SCALE, E_HSWISH, E_LOGITS, E_DHSWISH, E_PLAIN, E_DRELU };
 constexpr int LIN_T = 512;  // threads: eight waves, an eighth of k each
 struct Lin {
@@ -65,7 +66,9 @@ __global__ void __launch_bounds__(LIN_T) linear_small(const Lin p) {
     const int n = min(n0 + tok, p.N - 1);
     const int c1 = min(b0 + 16 + tok, p.ldb - 1);
     const float *x0 = p.X + b0 + tok, *x1 = p.X + c1;
-    f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+    f32x4 a0[2], a1[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) a0[h] = a1[h] = f32x4{0.f, 0.f, 0.f, 0.f};
     // 32 of k per turn, every load of a turn in flight before its first product.
     // K is a multiple of 8: a group of four is inside or outside as a whole.
     for (int k = k0; k < k1; k += 32) {
@@ -93,15 +96,16 @@ __global__ void __launch_bounds__(LIN_T) linear_small(const Lin p) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float w = on ? a[h][j] : 0.f;
-                a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(w, u[h][j], a0, 0, 0, 0);
-                a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(w, v[h][j], a1, 0, 0, 0);
+                a0[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, u[h][j], a0[h], 0, 0, 0);
+                a1[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, v[h][j], a1[h], 0, 0, 0);
             }
         }
     }
+    const f32x4 s0 = a0[0] + a0[1], s1 = a1[0] + a1[1];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        red[w][0][(4 * g + i) * 16 + tok] = a0[i];
-        red[w][1][(4 * g + i) * 16 + tok] = a1[i];
+        red[w][0][(4 * g + i) * 16 + tok] = s0[i];
+        red[w][1][(4 * g + i) * 16 + tok] = s1[i];
     }
     __syncthreads();
     const int half = threadIdx.x >> 8, e = threadIdx.x & 255;
@@ -157,7 +161,10 @@ __global__ void __launch_bounds__(1024) small_head(const float* __restrict__ f1,
     for (int b0 = 0; b0 < ldb; b0 += NB) {
         const int nb = min(NB, ldb - b0), nv = min(NB, B - b0);  // samples with padding, samples
         __syncthreads();
-        for (int e = t; e < F * nb; e += 1024) f[e / nb][e % nb] = f1[(int64_t)(e / nb) * ldb + b0 + e % nb];
+        for (int e = t; e < F * nb; e += 1024) {  // (f1's padding may hold anything)
+            const int k = e / nb, b = e % nb;
+            f[k][b] = b < nv ? f1[(int64_t)k * ldb + b0 + b] : 0.f;
+        }
         __syncthreads();
         for (int e = t; e < nv * C; e += 1024) {
             const int n = e / nv, b = e % nv;
@@ -202,9 +209,9 @@ __global__ void __launch_bounds__(1024) small_head(const float* __restrict__ f1,
             const int e = t + 1024 * i;
             float s = 0.f, u = 0.f;
             if (e < C * F) {
-                for (int b = 0; b < nv; b += 2) {  // (samples only: padding may hold anything)
+                for (int b = 0; b < nv; b += 2) {  // (an odd last sample is followed by zeros in both)
                     s = fmaf(dz[e / F][b], f[e % F][b], s);
-                    if (b + 1 < nv) u = fmaf(dz[e / F][b + 1], f[e % F][b + 1], u);
+                    u = fmaf(dz[e / F][b + 1], f[e % F][b + 1], u);
                 }
             } else if (e < C * F + C) {
                 for (int b = 0; b < nv; ++b) s += dz[e - C * F][b];
