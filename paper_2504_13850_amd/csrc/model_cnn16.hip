@@ -269,6 +269,11 @@ fo_status init(fo_model* m) {
     m->plan = P;
     const int B = m->max_batch;
     build(*P, m->cid, B);
+    // every convolution's weight gradient joins one set, and the update takes a
+    // range per convolution and one before, between and after them
+    static_assert(2 * kConvWgradMax + 1 <= kSgdSumsMax, "ranges of the update");
+    FO_CHECK(P->convs.size() <= kConvWgradMax, "cnn16: %zu convolutions, at most %d weight gradients in a set",
+             P->convs.size(), kConvWgradMax);
     Arena& a = m->arena;
     a.take<char>(sizeof(Plan) + 4096);
     size_t amax = (size_t)B * kHW * kHW * kIn, sw = 0, red = 0;
