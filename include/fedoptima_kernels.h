@@ -65,6 +65,17 @@ FO_API fo_status fo_conv2d_bf16(int32_t pass, int32_t Bn, int32_t H, int32_t W, 
                                 const uint16_t* in2, const uint16_t* w, const uint16_t* w_lo, float* out,
                                 int32_t splits, float* workspace, void* hip_stream);
 
+/* fo_conv2d_bf16's passes 0 and 1 as the CNN server steps run them: the sum over
+ * K is that of `splits` slices added in order, to the bit, whichever kernel
+ * runs (one that holds every slice of its tile adds them itself).  With
+ * slices_left (host) the sum over slices is left to the caller: *slices_left is
+ * the number of slices now in workspace, or 1 with the finished sum in out, where
+ * the slices were added one by one. */
+FO_API fo_status fo_conv2d_bf16_ordered(int32_t pass, int32_t Bn, int32_t H, int32_t W, int32_t Ci, int32_t Co,
+                                        int32_t k, int32_t stride, int32_t pad, const uint16_t* in,
+                                        const uint16_t* in_lo, const uint16_t* w, const uint16_t* w_lo, float* out,
+                                        int32_t splits, float* workspace, int32_t* slices_left, void* hip_stream);
+
 #ifdef __cplusplus
 }
 #endif

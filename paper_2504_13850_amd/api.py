@@ -26,8 +26,8 @@ EXPORTS = [
     "fo_queues_push", "fo_queues_push_model", "fo_pick_device", "fo_queues_in_service",
     "fo_queues_release", "fo_aggregate_pending", "fo_aggregate_pending_all", "fo_queues_stats",
     "fo_queues_counters", "fo_queues_add_device", "fo_last_error", "fo_profile_enable", "fo_profile_read",
-    "fo_set_graph_mode", "fo_gemm_bf16", "fo_conv2d_bf16", "fo_gemm_bf16_noalloc", "fo_queues_push_batch",
-    "fo_queues_push_model_batch", "fo_device_step", "fo_queues_set_policy", "fo_queues_set_device_active",
+    "fo_set_graph_mode", "fo_gemm_bf16", "fo_conv2d_bf16", "fo_conv2d_bf16_ordered", "fo_gemm_bf16_noalloc",
+    "fo_queues_push_batch", "fo_queues_push_model_batch", "fo_device_step", "fo_queues_set_policy", "fo_queues_set_device_active",
     "fo_queues_sender_status", "fo_queues_log_enable", "fo_queues_log_read", "fo_pipeline_run",
     "fo_net_units", "fo_select_split", "fo_aux_network",
 ]
@@ -150,6 +150,8 @@ def lib():
             "fo_gemm_bf16": (C.c_int, [i32, i32, i32, i32, vp, vp, i64, i32, vp, vp, i64, vp, i64, i32, vp, vp]),
             "fo_conv2d_bf16": (C.c_int, [i32, i32, i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, i32,
                                          vp, vp]),
+            "fo_conv2d_bf16_ordered": (C.c_int, [i32, i32, i32, i32, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, i32,
+                                                 vp, C.POINTER(i32), vp]),
             "fo_gemm_bf16_noalloc": (C.c_int, [i32, i32, i32, i32, vp, vp, i64, i32, vp, vp, i64, vp, i64, i32,
                                                vp]),
         }
@@ -478,3 +480,13 @@ def fo_conv2d_bf16(pass_, Bn, H, W, Ci, Co, k, stride, pad, inp, inp_lo, in2, w,
                    workspace=None, stream=None):
     _check(lib().fo_conv2d_bf16(pass_, Bn, H, W, Ci, Co, k, stride, pad, _dptr(inp), _dptr(inp_lo), _dptr(in2),
                                 _dptr(w), _dptr(w_lo), _dptr(out), splits, _dptr(workspace), _stream(stream)))
+
+
+def fo_conv2d_bf16_ordered(pass_, Bn, H, W, Ci, Co, k, stride, pad, inp, inp_lo, w, w_lo, out, splits, workspace,
+                           keep_slices=False, stream=None) -> int:
+    """The number of slices left in the workspace (keep_slices), else 1."""
+    left = C.c_int32(1)
+    _check(lib().fo_conv2d_bf16_ordered(pass_, Bn, H, W, Ci, Co, k, stride, pad, _dptr(inp), _dptr(inp_lo), _dptr(w),
+                                        _dptr(w_lo), _dptr(out), splits, _dptr(workspace),
+                                        C.byref(left) if keep_slices else None, _stream(stream)))
+    return left.value

@@ -88,11 +88,11 @@ extern "C" fo_status fo_gemm_bf16_noalloc(int32_t M, int32_t N, int32_t K, int32
     return fo_gemm_bf16(M, N, K, a_layout, A, A_lo, lda, b_layout, B, B_lo, ldb, C, ldc, splits, ws, hip_stream);
 }
 
-extern "C" fo_status fo_conv2d_bf16(int32_t pass, int32_t Bn, int32_t H, int32_t W, int32_t Ci, int32_t Co,
-                                    int32_t k, int32_t stride, int32_t pad, const uint16_t* in,
-                                    const uint16_t* in_lo, const uint16_t* in2, const uint16_t* w,
-                                    const uint16_t* w_lo, float* out, int32_t splits, float* workspace,
-                                    void* hip_stream) {
+// slices_left: NULL, or the slices are left in the workspace and their number is stored there.
+static fo_status conv2d(int32_t pass, int32_t Bn, int32_t H, int32_t W, int32_t Ci, int32_t Co, int32_t k,
+                        int32_t stride, int32_t pad, const uint16_t* in, const uint16_t* in_lo, const uint16_t* in2,
+                        const uint16_t* w, const uint16_t* w_lo, float* out, int32_t splits, float* workspace,
+                        bool ordered, int32_t* slices_left, void* hip_stream) {
     FO_CHECK(pass >= 0 && pass <= 2, "fo_conv2d_bf16: pass=%d", pass);
     FO_CHECK(Bn >= 1 && H >= 1 && W >= 1 && Ci >= 1 && Co >= 1 && k >= 1 && stride >= 1 && pad >= 0,
              "fo_conv2d_bf16: bad geometry");
@@ -128,5 +128,28 @@ extern "C" fo_status fo_conv2d_bf16(int32_t pass, int32_t Bn, int32_t H, int32_t
         d.bmode = OP_CONV_DWX; d.B = in2;
         d.ldcf = d.N;
     }
-    return gemm(d, (hipStream_t)hip_stream);
+    d.ordered = ordered;
+    d.defer_reduce = slices_left != nullptr;
+    const fo_status st = gemm(d, (hipStream_t)hip_stream);
+    if (st == FO_OK && slices_left) *slices_left = gemm_slices_left(d);
+    return st;
+}
+
+extern "C" fo_status fo_conv2d_bf16(int32_t pass, int32_t Bn, int32_t H, int32_t W, int32_t Ci, int32_t Co,
+                                    int32_t k, int32_t stride, int32_t pad, const uint16_t* in,
+                                    const uint16_t* in_lo, const uint16_t* in2, const uint16_t* w,
+                                    const uint16_t* w_lo, float* out, int32_t splits, float* workspace,
+                                    void* hip_stream) {
+    return conv2d(pass, Bn, H, W, Ci, Co, k, stride, pad, in, in_lo, in2, w, w_lo, out, splits, workspace, false,
+                  nullptr, hip_stream);
+}
+
+extern "C" fo_status fo_conv2d_bf16_ordered(int32_t pass, int32_t Bn, int32_t H, int32_t W, int32_t Ci, int32_t Co,
+                                            int32_t k, int32_t stride, int32_t pad, const uint16_t* in,
+                                            const uint16_t* in_lo, const uint16_t* w, const uint16_t* w_lo,
+                                            float* out, int32_t splits, float* workspace, int32_t* slices_left,
+                                            void* hip_stream) {
+    FO_CHECK(pass == 0 || pass == 1, "fo_conv2d_bf16_ordered: pass=%d", pass);
+    return conv2d(pass, Bn, H, W, Ci, Co, k, stride, pad, in, in_lo, nullptr, w, w_lo, out, splits, workspace, true,
+                  slices_left, hip_stream);
 }

@@ -182,3 +182,49 @@ def test_conv_passes(case):
             continue
         A.fo_conv2d_bf16(2, Bn, H, H, Ci, Co, k, st, pad, dyd, None, xd, None, None, dw, splits, ws)
         assert normwise(dw.cpu().numpy(), dw_ref) <= 1e-5, splits
+
+
+ORDERED = [  # (pass, Bn, H, Ci, Co, k, stride, low parts of the activations, slices)
+    (0, 64, 8, 256, 256, 3, 1, True, 4), (0, 64, 8, 128, 256, 3, 1, False, 5), (0, 64, 8, 256, 256, 3, 1, True, 7),
+    (0, 64, 8, 128, 256, 3, 1, False, 8), (0, 40, 9, 64, 256, 3, 1, True, 6), (0, 64, 8, 64, 256, 1, 1, True, 5),
+    (0, 64, 16, 64, 256, 3, 2, True, 8),
+    (1, 64, 8, 256, 256, 3, 1, False, 4), (1, 40, 9, 256, 192, 3, 1, False, 5), (1, 16, 16, 256, 128, 3, 2, False, 7),
+    (1, 64, 8, 256, 256, 3, 1, False, 8), (1, 64, 8, 256, 64, 1, 1, False, 6)]
+
+
+@pytest.mark.parametrize("case", ORDERED)
+def test_conv_ordered_slices(case):
+    """The same bits from the kernel that holds all slices of its 64 x 64 tile and from 128 x 128
+    tiles with a slice per workgroup, which a quarter of the images runs on: both where the
+    library adds the slices and where they are left to the caller, who adds them one by one."""
+    torch = torch_cuda()
+    pass_, Bn, H, Ci, Co, k, st, low, splits = case
+    announce(f"ordered conv {case}")
+    rng = np.random.default_rng(sum(case))
+    pad, Ho = k // 2, (H + 2 * (k // 2) - k) // st + 1
+    shape = (Bn, H, H, Ci) if pass_ == 0 else (Bn, Ho, Ho, Co)
+    xh, xl, _ = _split(rng, shape)
+    wh, wl, _ = _split(rng, (Co, k, k, Ci))
+    x, w = _dev16(xh), _dev16(wh)
+    xlo, wlo = _dev16(xl) if low else None, _dev16(wl) if pass_ == 0 else None
+    side, N = (Ho, Co) if pass_ == 0 else (H, Ci)
+
+    def run(i0, n, keep):
+        out = torch.full((n * side * side, N), 7.0, dtype=torch.float32, device="cuda")
+        ws = torch.zeros((splits, n * side * side, N), dtype=torch.float32, device="cuda")
+        part = slice(i0, i0 + n)
+        left = A.fo_conv2d_bf16_ordered(pass_, n, H, H, Ci, Co, k, st, pad, x[part], None if xlo is None else xlo[part],
+                                        w, wlo, out, splits, ws, keep)
+        if left > 1:
+            assert left == splits
+            out = ws[0].clone()
+            for z in range(1, splits):
+                out += ws[z]
+        return out.cpu().numpy(), left
+
+    for keep in (False, True):
+        got, left = run(0, Bn, keep)
+        quarters = [run(i, Bn // 4, keep) for i in range(0, Bn, Bn // 4)]
+        if keep:
+            assert left == 1 and all(q[1] == splits for q in quarters)  # both kernels ran
+        assert np.array_equal(got.view(np.uint32), np.concatenate([q[0] for q in quarters]).view(np.uint32)), keep
