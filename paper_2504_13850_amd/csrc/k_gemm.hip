@@ -2330,10 +2330,12 @@ void launch_ks(const GemmDesc& d, hipStream_t s) {
         dd.ordered = d.splits;
         dd.splits = 1;
         grid.z = 1;
-        if (d.splits > 4)
-            hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 8, true, LA, LB>), grid, dim3(512), 0, s, ea, eb, 0, dd);
-        else
-            hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 4, true, LA, LB>), grid, dim3(256), 0, s, ea, eb, 0, dd);
+        if constexpr (conv) {  // (gemm_tile: convolutions only)
+            if (d.splits > 4)
+                hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 8, true, LA, LB>), grid, dim3(512), 0, s, ea, eb, 0, dd);
+            else
+                hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 4, true, LA, LB>), grid, dim3(256), 0, s, ea, eb, 0, dd);
+        }
     } else if (eight)
         hipExtLaunchKernelGGL((gemm_ks_kernel<NSEG, 8, false, LA, LB>), grid, dim3(512), 0, s, ea, eb, 0, dd);
     else
@@ -2529,7 +2531,10 @@ static bool ks_form(const GemmDesc& d) {
 int gemm_tile(const GemmDesc& d) {
     if (!ks_form(d)) return BM;
     const int64_t big = cdiv(d.M, BM) * cdiv(d.N, BN), small = cdiv(d.M, SB) * cdiv(d.N, SB);
-    if (d.ordered) return !d.Mdev && d.splits >= 4 && d.splits <= 8 && small >= 192 && big <= 256 ? SB : BM;
+    if (d.ordered) {
+        const bool conv = d.amode == OP_CONV_FWD || d.amode == OP_CONV_DX;
+        return conv && !d.Mdev && d.splits >= 4 && d.splits <= 8 && small >= 192 && big <= 256 ? SB : BM;
+    }
     if (d.Mdev) return d.nseg == 1 && d.M <= 1536 ? SB : BM;
     return d.N <= SB || big <= 256 ? SB : BM;
 }
