@@ -1802,11 +1802,10 @@ __global__ void __launch_bounds__(NT, 2) gemm_rk_krt_dma_kernel(const GemmDesc d
 // workgroups of four waves per CU, or one of eight, cover each other's waits.  The
 // accumulators are added in LDS before the epilogue.
 // KT k per step: 32 with the low parts (four operand tiles), 64 without.
-// Bound by operand bytes: a step moves 16 KB per wave for 24 (16) MFMAs, and with
-// all CUs busy the copies reach 13-15 TB/s out of the L2s (90% hits); 128-byte
-// rows (64 k of the low parts too) moved no faster.  VGG-16 at batch 64, conv
-// 256 -> 256 on 8 x 8 maps: forward 25.7 us whole, against about 21 and a 7 us sum
-// of its slices; input gradient 14 against 18 + 7.
+// Bound by operand bytes: a step moves 16 KB per wave for 24 (16) MFMAs.  VGG-16 at
+// batch 64, conv 256 -> 256 on 8 x 8 maps: forward 27 us whole (302 MB of copies,
+// 11 TB/s, 94% of them L2 hits) against 24 and an 8 us sum of its slices on 128 x
+// 128 tiles; input gradient 14.6 against 21 + 8.
 constexpr int SB = 64;
 constexpr int kKsStage = 8192;  // bf16 elements of a wave's stage
 
@@ -2322,9 +2321,10 @@ void launch_ks(const GemmDesc& d, hipStream_t s) {
     dd.prof_snap = prof_snap(h);
     dim3 grid((d.N + SB - 1) / SB, (d.M + SB - 1) / SB, d.splits);
     // Eight waves where the launch leaves no CU a second workgroup (device step at
-    // batch 16 176 us against 178).  Packed rows only up to 256: their launches run beside
-    // the weight gradients, whose LDS leaves no room for 128 KB (transformer, both
-    // directions on small tiles, at batch 2 1712 against 1781 us, at 5 2136 against 1998).
+    // batch 16 174 us against 175).  Packed rows only up to 256: their launches run beside
+    // the weight gradients, whose LDS leaves no room for 128 KB (transformer at batch 1 and
+    // 2: 2132 and 2160 us against 2156 and 2172 with four; with eight up to 640 rows, at 4
+    // and 5: 2353 and 2356 against 2185 and 2264).
     const bool eight = d.Mdev ? d.M <= 256 : (int64_t)grid.x * grid.y * grid.z <= 256;
     if (d.ordered) {
         dd.ordered = d.splits;
@@ -2517,17 +2517,19 @@ static bool ks_form(const GemmDesc& d) {
            (d.g.stride == 1 || d.g.stride == 2);
 }
 // Where the line lies (a step, small tiles against 128 x 128):
-//  - ordered sums of 4 to 8 slices whose 64 x 64 tiles give (nearly) every CU one:
-//    a workgroup then holds all slices of its tile (VGG-16 at batch 64; with 64
-//    tiles, as ResNet-18 has, 858 us a step against 640 on unordered slices).
+//  - ordered sums of 4 to 8 slices (convolutions) whose 64 x 64 tiles give (nearly)
+//    every CU one: a workgroup then holds all slices of its tile.  VGG-16 at batch
+//    32, 64 and 128: 753, 900 and 1153 us a step on slices, 728, 823 and 1085 so; with
+//    64 tiles, as ResNet-18 has at batch 32, 845 against 839 on slices.
 //  - static sizes, up to 256 tiles of 128 x 128; past that the 128 x 128
 //    kernels fill the chip and read half the operand bytes.  An N of 64 leaves
-//    half of a 128-wide tile idle (device step 326 against 280 us).
+//    half of a 128-wide tile idle (device step at batch 64 and 128: 295 and 465
+//    against 279 and 428 us).
 //  - packed rows (the row count on the device, on average 0.63 of M), input
-//    gradients: up to M = 1536.  Transformer at batch 2, 5, 8 and 12: 2497,
-//    2546, 2609 and 2737 against 2193, 2339, 2506 and 2688 us; at 16 (M = 2048) small
-//    tiles lost, their launches beside the weight gradients being bound by bytes read.
-//    Compensated forwards keep the 128 x 128 tiles' order of summation.
+//    gradients: up to M = 1536.  Transformer at batch 2, 5, 8 and 12: 2484, 2476,
+//    2590 and 2688 us on 128 x 128 tiles, 2160, 2264, 2378 and 2645 on small ones; at 16
+//    (M = 2048) 2832 and 2821: the launches beside the weight gradients are bound by
+//    bytes read.  Compensated forwards keep the 128 x 128 tiles' order of summation.
 int gemm_tile(const GemmDesc& d) {
     if (!ks_form(d)) return BM;
     const int64_t big = cdiv(d.M, BM) * cdiv(d.N, BN), small = cdiv(d.M, SB) * cdiv(d.N, SB);
@@ -2540,8 +2542,8 @@ int gemm_tile(const GemmDesc& d) {
 }
 int gemm_slices_left(const GemmDesc& d) { return d.ordered && gemm_tile(d) == SB ? 1 : d.splits; }
 // As many slices as fit one round of workgroups (one per CU with 64 x 64 tiles,
-// two with 128 x 128), each at least 256 long (device step at batch 64 with one, two
-// workgroups per CU: 278 and 298 us).
+// two with 128 x 128), each at least 256 long (device step with one and two 64 x 64
+// workgroups per CU: 174 and 189 us at batch 16, 279 and 288 at 64).
 int gemm_splits(const GemmDesc& d, int maxs, int64_t ws_floats) {
     const int t = gemm_tile(d);
     const int64_t tiles = cdiv(d.M, t) * cdiv(d.N, t);

@@ -401,7 +401,8 @@ std::vector<int64_t> sgd_ranges(const LayerOff* off, int64_t pool_w) {
 
 // K slices (at most) of the products with N = D whose sum a norm takes: two time
 // like four where the launch fills the chip and halve the norm's reads; on 64 x 64
-// tiles four are better (batch 3: 1828 against 1677 us a step).
+// tiles four are better at the smallest batches (1, 2 and 3: 2132, 2160 and 2201 us a
+// step against 2142, 2178 and 2257 with two; at 5 and 8 2264 and 2378 against 2247 and 2360).
 int slices(const GemmDesc& d) { return gemm_tile(d) == 64 ? 4 : 2; }
 
 size_t ws_bytes(const fo_model* m) {

@@ -187,11 +187,14 @@ void build(Plan& P, int cid, int B) {
         f.b = o; o += f.out;
         P.fcs.push_back(f);
     }
-    // Weight gradients: slices about as long as give two rounds of two
-    // workgroups per CU over all layers together (VGG at batch 64: 33,600 tile
-    // steps, so 1,024 pixels; shorter ones write more partial sums, longer ones
-    // leave the last round unbalanced), at least 256 pixels so that a
-    // workgroup's ring fill stays small against its walk.
+    // Weight gradients: slices of the shortest power of two of tile steps that gives
+    // at most two rounds of two workgroups per CU (1,024, and the rests at the end of
+    // each product) over all layers together: VGG-16 at batch 64, 33,664 tile steps,
+    // takes 64 (2,048 pixels), ResNet-18 at 32, 6,208, takes 8 (256 pixels).  Shorter
+    // ones write more partial sums, longer ones leave the last round unbalanced (the
+    // power nearest to steps / 1,024: VGG-16 at batch 20, 32 and 64 679, 716 and 795 us a
+    // step against 662, 723 and 818).  From 256 pixels, so that a workgroup's ring
+    // fill stays small against its walk, to 2,048.
     int64_t steps = 0;
     for (const Conv& c : P.convs)
         steps += cdiv(c.cout, 128) * cdiv(c.k * c.k * c.cin, 128) * cdiv((int64_t)B * c.Ho * c.Wo, kConvWgradK);

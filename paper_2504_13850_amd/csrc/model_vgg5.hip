@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(256) bn5_bwd(const float* __restrict__ dy, con
 
 // ------------------------------------------------------------------ the fused step, batches of up to 128
 // With a launch per product, norm and pool the step is 23 dependent launches of
-// 4.5 us or little more (120.6 us at batch 32).  Here it is 8 (65.5 us): the convolution as an implicit GEMM of
+// 4.5 us or little more (120.6 us at batch 32).  Here it is 8 (64.5 us): the convolution as an implicit GEMM of
 // one image in LDS; batch norm, ReLU and pool by the workgroup that owns a
 // channel over the whole batch; fc1; one workgroup for everything between the
 // hidden layer and its gradient; the pooled gradient of a channel (a 16-column
