@@ -228,3 +228,43 @@ def test_conv_ordered_slices(case):
         if keep:
             assert left == 1 and all(q[1] == splits for q in quarters)  # both kernels ran
         assert np.array_equal(got.view(np.uint32), np.concatenate([q[0] for q in quarters]).view(np.uint32)), keep
+
+
+GEOMETRIES = [  # (Bn, H, W, Ci, Co, k, stride, pad): odd maps, even and wide filters, no and wide padding, strides
+    (3, 7, 10, 64, 72, 3, 1, 1), (2, 9, 5, 64, 64, 5, 1, 2), (2, 8, 11, 128, 64, 2, 2, 0), (3, 11, 7, 64, 128, 3, 2, 1),
+    (1, 13, 6, 192, 64, 5, 2, 3), (2, 12, 9, 64, 64, 3, 3, 1), (5, 3, 3, 64, 64, 1, 1, 0), (2, 5, 8, 64, 64, 3, 1, 3),
+    (1, 4, 4, 64, 64, 4, 1, 0)]
+
+
+@pytest.mark.parametrize("case", GEOMETRIES)
+def test_conv_geometries(case):
+    """Compensated forward, with and without the activations' low parts, and input gradient,
+    unsplit and in slices, on 64 x 64 tiles (strides 1 and 2) and 128 x 128 ones."""
+    torch = torch_cuda()
+    Bn, H, W, Ci, Co, k, st, pad = case
+    announce(f"conv geometry {case}")
+    rng = np.random.default_rng(sum(case))
+    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    xh, xl, xv = _split(rng, (Bn, H, W, Ci))
+    wh, wl, wv = _split(rng, (Co, k, k, Ci))
+    dy, dyv = _bf16(rng, (Bn, Ho, Wo, Co))
+    for low in (True, False):
+        x = xv if low else S.f32_from_bf16_bits(xh).astype(np.float64)
+        conv = OL.Conv2d(wv.transpose(0, 3, 1, 2), None, st, pad)
+        ref = conv.fwd(x.transpose(0, 3, 1, 2)).transpose(0, 2, 3, 1)
+        for splits in (1, 3):
+            ws = torch.empty(splits * ref.size, dtype=torch.float32, device="cuda")
+            y = torch.zeros(ref.shape, dtype=torch.float32, device="cuda")
+            A.fo_conv2d_bf16(0, Bn, H, W, Ci, Co, k, st, pad, _dev16(xh), _dev16(xl) if low else None, None, _dev16(wh),
+                             _dev16(wl), y, splits, ws)
+            assert normwise(y.cpu().numpy(), ref) <= 2e-5, (low, splits)
+    if Co % 64:
+        return
+    conv = OL.Conv2d(S.f32_from_bf16_bits(wh).astype(np.float64).transpose(0, 3, 1, 2), None, st, pad)
+    conv.fwd(xv.transpose(0, 3, 1, 2))
+    ref = conv.bwd(dyv.transpose(0, 3, 1, 2)).transpose(0, 2, 3, 1)
+    for splits in (1, 3):
+        ws = torch.empty(splits * ref.size, dtype=torch.float32, device="cuda")
+        dx = torch.zeros(ref.shape, dtype=torch.float32, device="cuda")
+        A.fo_conv2d_bf16(1, Bn, H, W, Ci, Co, k, st, pad, _dev16(dy), None, None, _dev16(wh), None, dx, splits, ws)
+        assert normwise(dx.cpu().numpy(), ref) <= 1e-5, splits
