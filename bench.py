@@ -837,7 +837,7 @@ def main():
                     "avg_launch_us": round(dom["ms"] / dom["launches"] * 1e3, 2), "traffic": traffic_for(dom["name"]),
                     "traffic_source": TRAFFIC_SOURCE}
     else:  # the fp32 direct-convolution CNN: the whole step against the fp32 vector peak
-        roofline = {"bound": "alu", "kernel": "whole step (fp32 FMA kernels, not instrumented)",
+        roofline = {"bound": "alu", "kernel": "whole step (fp32 kernels, not instrumented)",
                     "achieved": round(flops_step / (ms_step * 1e-3) / 1e12, 3), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(mfu, 5), "traffic": None}
     kernels = [{"name": s["name"], "launches": s["launches"], "ms_per_step": round(s["ms"] / args.steps, 4),

@@ -1802,10 +1802,10 @@ __global__ void __launch_bounds__(NT, 2) gemm_rk_krt_dma_kernel(const GemmDesc d
 // workgroups of four waves per CU, or one of eight, cover each other's waits.  The
 // accumulators are added in LDS before the epilogue.
 // KT k per step: 32 with the low parts (four operand tiles), 64 without.
-// Bound by operand bytes: a step moves 16 KB per wave for 24 (16) MFMAs.  VGG-16 at
-// batch 64, conv 256 -> 256 on 8 x 8 maps: forward 27 us whole (302 MB of copies,
-// 11 TB/s, 94% of them L2 hits) against 24 and an 8 us sum of its slices on 128 x
-// 128 tiles; input gradient 14.6 against 21 + 8.
+// Bound by operand bytes: a step moves 16 KB per wave for 24 (16) MFMAs, and the L2s
+// answer 8 TB/s of 64-byte requests, 94% hits, beside 18% of the MFMA peak.  VGG-16
+// at batch 64, conv 256 -> 256 on 8 x 8 maps: forward 27 us whole against 24 and an
+// 8 us sum of its slices on 128 x 128 tiles; input gradient 14.6 against 21 + 8.
 constexpr int SB = 64;
 constexpr int kKsStage = 8192;  // bf16 elements of a wave's stage
 
