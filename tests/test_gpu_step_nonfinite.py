@@ -77,3 +77,28 @@ def test_no_trace_of_a_nonfinite_step(cid, how):
         finally:
             A.fo_model_destroy(model)
             A.fo_model_destroy(fresh)
+
+
+@pytest.mark.parametrize("cid", sorted(CASES))
+def test_new_model_in_used_memory(cid):
+    """A workspace is not cleared at creation: a model created where another one left NaN steps
+    like one created before."""
+    torch = torch_cuda()
+    full, shorter = CASES[cid]
+    theta = S.init_params(cid)
+    stream = torch.cuda.current_stream()
+    batch = _batch(torch, cid, shorter[-1], 90)
+    fresh = A.fo_model_create(cid, full, theta, stream)
+    want = _step(torch, fresh, cid, batch)
+    A.fo_model_destroy(fresh)
+    announce(f"config {cid} batch {shorter[-1]} in used memory")
+    used = A.fo_model_create(cid, full, theta, stream)
+    _poison(torch, used, cid, theta, _batch(torch, cid, full, 70), "nan")
+    A.fo_model_destroy(used)
+    again = A.fo_model_create(cid, full, theta, stream)
+    try:
+        got = _step(torch, again, cid, batch)
+        for k, v in want.items():
+            assert np.array_equal(got[k].view(np.uint32), v.view(np.uint32)), k
+    finally:
+        A.fo_model_destroy(again)
